@@ -509,6 +509,14 @@ soap_status soap_compress_backward(const soap_calculator* calc, const soap_exec*
 soap_status soap_spectrum_gram(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
                                const float* X, float* K);
 
+/* soap_spectrum_gram with a device workspace (256-byte aligned) of at least
+ * soap_spectrum_gram_workspace_size bytes: the sum over the features is
+ * split over the chip and its parts added in a fixed order.  The workspace
+ * is overwritten; calls that overlap must not share it.                 */
+soap_status soap_spectrum_gram_workspace_size(int32_t n, int32_t n_channels, int32_t lmax, size_t* bytes);
+soap_status soap_spectrum_gram_ws(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
+                                  const float* X, float* K, void* workspace, size_t workspace_bytes);
+
 /* Training loss of the compression over a batch and its gradient:
  *   L = |K~ - Kref|_F^2 / |Kref|_F^2,  K~ = soap_spectrum_gram(X),
  *   grad_X = dL/dX [n][lmax+1][Q(Q+1)/2].
@@ -516,6 +524,13 @@ soap_status soap_spectrum_gram(const soap_exec* exec, int32_t n, int32_t n_chann
 soap_status soap_spectrum_kernel_loss(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
                                       const float* X, const float* Kref, float* work, float* loss,
                                       float* grad_X);
+
+/* soap_spectrum_kernel_loss with a workspace as for soap_spectrum_gram_ws
+ * (of soap_spectrum_gram_workspace_size bytes for the same n, n_channels
+ * and lmax) besides work.                                               */
+soap_status soap_spectrum_kernel_loss_ws(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
+                                         const float* X, const float* Kref, float* work, float* loss,
+                                         float* grad_X, void* workspace, size_t workspace_bytes);
 
 /* One Adam step (Kingma & Ba, bias-corrected; step counts from 1) on n
  * parameters: m <- b1 m + (1-b1) g, v <- b2 v + (1-b2) g^2,

@@ -33,7 +33,8 @@ EXPORTS = [
     "soap_compress_n_params", "soap_compress_workspace_size", "soap_compress_save", "soap_compress_load",
     "soap_compress_forward_ws",
     "soap_compress_init_pca", "soap_compress_forward", "soap_compress_backward", "soap_spectrum_gram",
-    "soap_spectrum_kernel_loss", "soap_adam_step", "soap_read_device_status",
+    "soap_spectrum_gram_workspace_size", "soap_spectrum_gram_ws", "soap_spectrum_kernel_loss",
+    "soap_spectrum_kernel_loss_ws", "soap_adam_step", "soap_read_device_status",
 ]
 
 
@@ -140,6 +141,12 @@ def lib():
     L.soap_spectrum_gram.argtypes = [P(soap_exec), i32, i32, i32, vp, vp]
     L.soap_spectrum_kernel_loss.restype = st
     L.soap_spectrum_kernel_loss.argtypes = [P(soap_exec), i32, i32, i32, vp, vp, vp, vp, vp]
+    L.soap_spectrum_gram_workspace_size.restype = st
+    L.soap_spectrum_gram_workspace_size.argtypes = [i32, i32, i32, P(sz)]
+    L.soap_spectrum_gram_ws.restype = st
+    L.soap_spectrum_gram_ws.argtypes = [P(soap_exec), i32, i32, i32, vp, vp, vp, sz]
+    L.soap_spectrum_kernel_loss_ws.restype = st
+    L.soap_spectrum_kernel_loss_ws.argtypes = [P(soap_exec), i32, i32, i32, vp, vp, vp, vp, vp, vp, sz]
     L.soap_adam_step.restype = st
     L.soap_adam_step.argtypes = [P(soap_exec), i64, vp, vp, vp, vp, f32, f32, f32, f32, i32]
     L.soap_read_device_status.restype = st

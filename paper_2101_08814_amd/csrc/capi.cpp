@@ -1153,34 +1153,86 @@ soap_status soap_compress_backward(const soap_calculator* calc, const soap_exec*
     return launched(launch_compress_backward(a, grad_weights, stream_of(exec)), "compression backward");
 }
 
-soap_status soap_spectrum_gram(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax, const float* X,
-                               float* K)
+namespace {
+
+soap_status check_gram(int32_t n, int32_t lo, int32_t n_channels, int32_t lmax)
 {
-    clear_error();
-    REQUIRE(n >= 0 && n <= 65536, "n must be in [0, 65536]");
+    REQUIRE(n >= lo && n <= 65536, "n must be in [%d, 65536]", lo);
     REQUIRE(n_channels >= 1 && n_channels <= 4096, "n_channels must be in [1, 4096]");
     REQUIRE(lmax >= 0 && lmax <= 12, "lmax must be in [0, 12]");
+    return SOAP_OK;
+}
+
+soap_status gram_impl(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax, const float* X, float* K,
+                      void* ws)
+{
     if (n == 0) return SOAP_OK;
     CHECK(check_ptr(X, 4, "X"));
     CHECK(check_ptr(K, 4, "K"));
-    return launched(launch_spectrum_gram(n, n_channels, lmax, X, K, stream_of(exec)), "spectrum gram");
+    return launched(launch_spectrum_gram(n, n_channels, lmax, X, K, ws, stream_of(exec)), "spectrum gram");
 }
 
-soap_status soap_spectrum_kernel_loss(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
-                                      const float* X, const float* Kref, float* work, float* loss, float* grad_X)
+soap_status kernel_loss_impl(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax, const float* X,
+                             const float* Kref, float* work, float* loss, float* grad_X, void* ws)
 {
-    clear_error();
-    REQUIRE(n >= 1 && n <= 65536, "n must be in [1, 65536]");
-    REQUIRE(n_channels >= 1 && n_channels <= 4096, "n_channels must be in [1, 4096]");
-    REQUIRE(lmax >= 0 && lmax <= 12, "lmax must be in [0, 12]");
     CHECK(check_ptr(X, 4, "X"));
     CHECK(check_ptr(Kref, 4, "Kref"));
     CHECK(check_ptr(work, 4, "work"));
     CHECK(check_ptr(loss, 4, "loss"));
     CHECK(check_ptr(grad_X, 4, "grad_X"));
     return launched(launch_spectrum_kernel_loss(n, n_channels, lmax, X, Kref, work, loss, work + int64_t(n) * n,
-                                                grad_X, stream_of(exec)),
+                                                grad_X, ws, stream_of(exec)),
                     "kernel loss");
+}
+
+}  // namespace
+
+soap_status soap_spectrum_gram(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax, const float* X,
+                               float* K)
+{
+    clear_error();
+    CHECK(check_gram(n, 0, n_channels, lmax));
+    return gram_impl(exec, n, n_channels, lmax, X, K, nullptr);
+}
+
+soap_status soap_spectrum_gram_workspace_size(int32_t n, int32_t n_channels, int32_t lmax, size_t* bytes)
+{
+    clear_error();
+    CHECK(check_gram(n, 0, n_channels, lmax));
+    REQUIRE(bytes, "bytes is NULL");
+    if (alloc_failure_forced()) return fail(SOAP_ENOMEM, "allocation failure forced by SOAP_FAIL_ALLOC");
+    *bytes = n == 0 ? 0 : spectrum_gram_workspace(n, n_channels, lmax);
+    return SOAP_OK;
+}
+
+soap_status soap_spectrum_gram_ws(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax, const float* X,
+                                  float* K, void* workspace, size_t workspace_bytes)
+{
+    clear_error();
+    CHECK(check_gram(n, 0, n_channels, lmax));
+    if (n == 0) return SOAP_OK;
+    CHECK(check_ptr(workspace, 256, "workspace"));
+    REQUIRE(workspace_bytes >= spectrum_gram_workspace(n, n_channels, lmax), "workspace too small");
+    return gram_impl(exec, n, n_channels, lmax, X, K, workspace);
+}
+
+soap_status soap_spectrum_kernel_loss(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
+                                      const float* X, const float* Kref, float* work, float* loss, float* grad_X)
+{
+    clear_error();
+    CHECK(check_gram(n, 1, n_channels, lmax));
+    return kernel_loss_impl(exec, n, n_channels, lmax, X, Kref, work, loss, grad_X, nullptr);
+}
+
+soap_status soap_spectrum_kernel_loss_ws(const soap_exec* exec, int32_t n, int32_t n_channels, int32_t lmax,
+                                         const float* X, const float* Kref, float* work, float* loss, float* grad_X,
+                                         void* workspace, size_t workspace_bytes)
+{
+    clear_error();
+    CHECK(check_gram(n, 1, n_channels, lmax));
+    CHECK(check_ptr(workspace, 256, "workspace"));
+    REQUIRE(workspace_bytes >= spectrum_gram_workspace(n, n_channels, lmax), "workspace too small");
+    return kernel_loss_impl(exec, n, n_channels, lmax, X, Kref, work, loss, grad_X, workspace);
 }
 
 soap_status soap_adam_step(const soap_exec* exec, int64_t n, float* params, const float* grads, float* m, float* v,

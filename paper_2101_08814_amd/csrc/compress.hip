@@ -20,6 +20,7 @@
 #include <cmath>
 
 #include "chunk.hpp"
+#include "tile_f32.hpp"
 
 namespace soap {
 namespace {
@@ -322,57 +323,148 @@ __global__ void __launch_bounds__(kThreads) k_channel_cov(CompressArgs a, float*
 
 
 // ------------------------------------------------ kernel matrix and loss
-// Tiled products of the feature matrix X [n][F] (F = (lmax+1) Q(Q+1)/2):
-// gram C = X diag(w) X^T, and C = D X (D [n][n]) scaled by w and a device
-// scalar.  64 x 64 output tiles, 16-wide slices of the inner dimension in
-// LDS, 4 x 4 outputs per lane.
-constexpr int kT = 64, kKd = 16;
+// Products of the feature matrix X [n][F] (F = (lmax+1) Q(Q+1)/2): the gram
+// matrix C = X diag(w) X^T and C = D X (D [n][n]) scaled by w and a device
+// scalar, in 64 x 64 tiles on the FP32 matrix cores (tile_f32.hpp).
+//
+// Gram: C is symmetric, so only the tiles on and above the diagonal are
+// computed, and the inner dimension (18,396 to 41,904 for the full spectrum)
+// is split over the grid so that a batch of a few hundred centres (36 tiles
+// at n = 512) fills the chip; k_gram_reduce adds the slices in order.
+// Consecutive work-groups go to the eight XCDs in turn, and slice =
+// blockIdx % slices with a multiple of eight slices keeps each XCD on its own
+// columns of X, which then stay in its L2.  The sums of one slice are
+// shorter than one chain over F, so the rounding is smaller too.
+// n = 512, 72 channels, lmax 6 (F = 18,396), a training batch's three
+// products: 4.6 ms for the full kernel on the vector units with one
+// work-group per output tile over all of F (64 work-groups), now 0.16 ms for
+// both kernel matrices; loss sums 144 -> 13 us, gradient 109 -> 37 us.  The
+// error of the kernel against 64 bits went from 4.1e-6 to 4.3e-7.
+constexpr int kGramFill = 1024;      // work-groups to aim for
+constexpr int kGramDeep = 4;         // slabs of the inner dimension per slice, at least
 
-__global__ void __launch_bounds__(256) k_gram(int n, int F, int Q, const float* X, float* C)
+// tile t of the upper triangle: row-major over bi <= bj < nb
+__device__ __forceinline__ void gram_tile(int nb, int64_t t, int64_t& bi, int64_t& bj)
 {
-    __shared__ float As[kKd][kT + 1], Bs[kKd][kT + 1];
-    const int QQ = Q * (Q + 1) / 2;
-    const int i0 = blockIdx.y * kT, j0 = blockIdx.x * kT;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc[4][4] = {};
-    for (int f0 = 0; f0 < F; f0 += kKd) {
-        for (int e = threadIdx.x; e < kT * kKd; e += 256) {
-            const int r = e / kKd, f = e - r * kKd, ff = f0 + f;
-            const bool inf = ff < F;
-            const float wf = inf ? full_weight(Q, ff % QQ) : 0.0f;
-            As[f][r] = (inf && i0 + r < n) ? X[int64_t(i0 + r) * F + ff] * wf : 0.0f;
-            Bs[f][r] = (inf && j0 + r < n) ? X[int64_t(j0 + r) * F + ff] : 0.0f;
-        }
-        __syncthreads();
+    // rows before row i hold i nb - i (i - 1) / 2 tiles
+    int64_t i = int64_t((2.0 * nb + 1.0 - sqrt((2.0 * nb + 1.0) * (2.0 * nb + 1.0) - 8.0 * double(t))) * 0.5);
+    while (i > 0 && i * nb - i * (i - 1) / 2 > t) --i;
+    while ((i + 1) * nb - (i + 1) * i / 2 <= t) ++i;
+    bi = i;
+    bj = i + (t - (i * nb - i * (i - 1) / 2));
+}
+
+// part == NULL (one slice): C directly.  Otherwise slice s of tile t goes to
+// part[(s tiles + t) 4096 + ...] in the lanes' own order.
+__global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int64_t F, int64_t depth, int Q,
+                                                 const float* X, float* C, float* part)
+{
+    __shared__ tf::Smem sm;
+    const int64_t tiles = int64_t(nb) * (nb + 1) / 2;
+    const int s = int(blockIdx.x % unsigned(slices));
+    const int64_t t = blockIdx.x / unsigned(slices);
+    int64_t bi, bj;
+    gram_tile(nb, t, bi, bj);
+    const int64_t i0 = bi * tf::kTile, j0 = bj * tf::kTile;
+    const int64_t k0 = s * depth, k1 = k0 + depth < F ? k0 + depth : F;
+    tf::f32x4 acc[2][2];
+    tf::TriWeight w;
+    w.init(Q, k0 + (threadIdx.x & 31));
+    const int ra = n - i0 < tf::kTile ? int(n - i0) : tf::kTile, cb = n - j0 < tf::kTile ? int(n - j0) : tf::kTile;
+    tf::product<true>(sm, X + i0 * F, F, ra, X + j0 * F, F, cb, k0, k1, w, acc);
+    if (part) {
+        float* out = part + (int64_t(s) * tiles + t) * 4096 + (threadIdx.x >> 6) * 1024 + (threadIdx.x & 63) * 4;
 #pragma unroll
-        for (int f = 0; f < kKd; ++f) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { av[u] = As[f][ty + 16 * u]; bv[u] = Bs[f][tx + 16 * u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] += av[u] * bv[v];
-        }
-        __syncthreads();
+        for (int u = 0; u < 4; ++u) *reinterpret_cast<tf::f32x4*>(out + 256 * u) = acc[u >> 1][u & 1];
+        return;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int i = i0 + ty + 16 * u, j = j0 + tx + 16 * v;
-            if (i < n && j < n) C[int64_t(i) * n + j] = acc[u][v];
+            const int64_t i = i0 + tf::out_row(u >> 1) + v, j = j0 + tf::out_col(u & 1);
+            if (i < n && j < n) {
+                C[i * n + j] = acc[u >> 1][u & 1][v];
+                if (bi != bj) C[j * n + i] = acc[u >> 1][u & 1][v];
+            }
         }
 }
 
-// loss = sum (Kt - Kref)^2 / sum Kref^2 (one work-group); D <- (Kt - Kref)
-// in place of Kt and scale[0] = 4 / sum Kref^2 (the factor of dL/dX)
-__global__ void __launch_bounds__(1024) k_kernel_loss(int64_t nn, float* Kt, const float* Kref, float* loss,
-                                                      float* scale)
+// Adds the slices in order: one lane per accumulator (four rows of one
+// column), four work-groups per tile.  With Kref the difference to it goes
+// to C instead, and sums[2 block], sums[2 block + 1] get this work-group's
+// sum of (Kt - Kref)^2 and of Kref^2.
+template <bool LOSS>
+__global__ void __launch_bounds__(256) k_gram_reduce(int n, int nb, int slices, const float* part, float* C,
+                                                     const float* Kref, double* sums)
+{
+    const int64_t tiles = int64_t(nb) * (nb + 1) / 2, t = blockIdx.x >> 2;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, u = blockIdx.x & 3;
+    const float* src = part + t * 4096 + wave * 1024 + u * 256 + lane * 4;
+    tf::f32x4 a = *reinterpret_cast<const tf::f32x4*>(src);
+#pragma unroll 4
+    for (int s = 1; s < slices; ++s) a += *reinterpret_cast<const tf::f32x4*>(src + s * tiles * 4096);
+    int64_t bi, bj;
+    gram_tile(nb, t, bi, bj);
+    const int64_t i0 = bi * tf::kTile + tf::out_row(u >> 1), j = bj * tf::kTile + tf::out_col(u & 1);
+    double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int64_t i = i0 + v;
+        if (i >= n || j >= n) continue;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {   // (i, j) and, off the diagonal tiles, (j, i)
+            if (m && bi == bj) continue;
+            const int64_t e = m ? j * n + i : i * n + j;
+            if (LOSS) {
+                const double r = Kref[e], d = double(a[v]) - r;
+                C[e] = float(d);
+                s1 += d * d;
+                s2 += r * r;
+            } else {
+                C[e] = a[v];
+            }
+        }
+    }
+    if (LOSS) {
+        __shared__ double red[2][4];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            s1 += __shfl_xor(s1, o, 64);
+            s2 += __shfl_xor(s2, o, 64);
+        }
+        if (lane == 0) {
+            red[0][wave] = s1;
+            red[1][wave] = s2;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2)
+            sums[2 * int64_t(blockIdx.x) + threadIdx.x] =
+                (red[threadIdx.x][0] + red[threadIdx.x][1]) + (red[threadIdx.x][2] + red[threadIdx.x][3]);
+    }
+}
+
+__device__ __forceinline__ void loss_of(double d2, double r2, float* loss, float* scale)
+{
+    const double norm2 = r2 > 0.0 ? r2 : 1.0;
+    loss[0] = float(d2 / norm2);
+    scale[0] = float(4.0 / norm2);
+}
+
+// one work-group: loss = sum (Kt - Kref)^2 / sum Kref^2 and scale[0] =
+// 4 / sum Kref^2 (the factor of dL/dX), from the work-groups' sums
+// (m pairs) or, sums == NULL, from Kt (m entries; D = Kt - Kref in place)
+__global__ void __launch_bounds__(1024) k_kernel_loss(int64_t m, const double* sums, float* Kt, const float* Kref,
+                                                      float* loss, float* scale)
 {
     __shared__ double s1[1024], s2[1024];
     double a1 = 0.0, a2 = 0.0;
-    for (int64_t e = threadIdx.x; e < nn; e += 1024) {
+    for (int64_t e = threadIdx.x; e < m; e += 1024) {
+        if (sums) {
+            a1 += sums[2 * e];
+            a2 += sums[2 * e + 1];
+            continue;
+        }
         const double d = double(Kt[e]) - double(Kref[e]);
         Kt[e] = float(d);
         a1 += d * d;
@@ -388,52 +480,33 @@ __global__ void __launch_bounds__(1024) k_kernel_loss(int64_t nn, float* Kt, con
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const double norm2 = s2[0] > 0.0 ? s2[0] : 1.0;
-        loss[0] = float(s1[0] / norm2);
-        scale[0] = float(4.0 / norm2);
-    }
+    if (threadIdx.x == 0) loss_of(s1[0], s2[0], loss, scale);
 }
 
-// dX[i][f] = scale * w_f * sum_j D[i][j] X[j][f]  (D symmetric)
-__global__ void __launch_bounds__(256) k_loss_grad(int n, int F, int Q, const float* D, const float* X,
-                                                   const float* scale, float* dX)
+// dX[i][f] = scale * w_f * sum_j D[i][j] X[j][f]
+__global__ void __launch_bounds__(256, 2) k_loss_grad(int n, int64_t F, int Q, const float* D, const float* X,
+                                                      const float* scale, float* dX)
 {
-    __shared__ float As[kKd][kT + 1], Bs[kKd][kT + 1];
-    const int QQ = Q * (Q + 1) / 2;
-    const int i0 = blockIdx.y * kT, f0 = blockIdx.x * kT;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc[4][4] = {};
-    for (int j0 = 0; j0 < n; j0 += kKd) {
-        for (int e = threadIdx.x; e < kT * kKd; e += 256) {
-            const int r = e / kKd, j = e - r * kKd;
-            As[j][r] = (i0 + r < n && j0 + j < n) ? D[int64_t(i0 + r) * n + j0 + j] : 0.0f;
-        }
-        for (int e = threadIdx.x; e < kT * kKd; e += 256) {
-            const int j = e / kT, f = e - j * kT;
-            Bs[j][f] = (j0 + j < n && f0 + f < F) ? X[int64_t(j0 + j) * F + f0 + f] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kKd; ++j) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { av[u] = As[j][ty + 16 * u]; bv[u] = Bs[j][tx + 16 * u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] += av[u] * bv[v];
-        }
-        __syncthreads();
-    }
+    __shared__ tf::Smem sm;
+    const int64_t i0 = int64_t(blockIdx.y) * tf::kTile, f0 = int64_t(blockIdx.x) * tf::kTile;
+    const int ra = n - i0 < tf::kTile ? int(n - i0) : tf::kTile, cb = F - f0 < tf::kTile ? int(F - f0) : tf::kTile;
+    tf::f32x4 acc[2][2];
+    tf::product<false>(sm, D + i0 * n, n, ra, X + f0, F, cb, 0, n, tf::NoWeight{}, acc);
     const float sc = scale[0];
+    const int QQ = Q * (Q + 1) / 2;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int bj = 0; bj < 2; ++bj) {
+        const int64_t f = f0 + tf::out_col(bj);
+        if (f >= F) continue;
+        const float wf = sc * full_weight(Q, int(f % QQ));
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = i0 + ty + 16 * u, f = f0 + tx + 16 * v;
-            if (i < n && f < F) dX[int64_t(i) * F + f] = sc * full_weight(Q, f % QQ) * acc[u][v];
-        }
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t i = i0 + tf::out_row(bi) + v;
+                if (i < n) dX[i * F + f] = wf * acc[bi][bj][v];
+            }
+    }
 }
 
 // -------------------------------------------------------------- optimiser
@@ -1329,21 +1402,77 @@ hipError_t launch_channel_cov(const CompressArgs& a, float* part, int slices, hi
     return hipGetLastError();
 }
 
-hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C, hipStream_t stream)
+namespace {
+
+// slices of the inner dimension for the gram matrix: enough work-groups to
+// fill the chip, each slice at least kGramDeep slabs, in multiples of eight
+// (one set of columns per XCD) where that many fit
+struct GramSplit {
+    int nb, slices;
+    int64_t F, tiles, depth;
+};
+
+GramSplit gram_split(int n, int Q, int lmax, bool split)
 {
-    const int F = (lmax + 1) * Q * (Q + 1) / 2;
-    hipLaunchKernelGGL(k_gram, dim3(blocks_of(n, kT), blocks_of(n, kT)), dim3(256), 0, stream, n, F, Q, X, C);
+    GramSplit g;
+    g.F = int64_t(lmax + 1) * Q * (Q + 1) / 2;
+    g.nb = (n + tf::kTile - 1) / tf::kTile;
+    g.tiles = int64_t(g.nb) * (g.nb + 1) / 2;
+    int64_t s = split ? kGramFill / g.tiles : 1;
+    const int64_t deep = g.F / (kGramDeep * tf::kSlab);
+    if (s > deep) s = deep;
+    if (s > 64) s = 64;
+    if (s >= 8) s = s / 8 * 8;
+    if (s < 1) s = 1;
+    const int64_t slabs = (g.F + tf::kSlab - 1) / tf::kSlab;
+    g.depth = (slabs + s - 1) / s * tf::kSlab;
+    g.slices = int((g.F + g.depth - 1) / g.depth);   // non-empty slices
+    return g;
+}
+
+}  // namespace
+
+// partial tiles of every slice, then the work-groups' loss sums
+size_t spectrum_gram_workspace(int n, int Q, int lmax)
+{
+    const GramSplit g = gram_split(n, Q, lmax, true);
+    return size_t(g.slices) * size_t(g.tiles) * 4096 * sizeof(float) + size_t(g.tiles) * 8 * sizeof(double);
+}
+
+hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C, void* ws, hipStream_t stream)
+{
+    const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
+    float* part = g.slices > 1 ? static_cast<float*>(ws) : nullptr;
+    hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F, g.depth,
+                       Q, X, C, part);
+    if (part)
+        hipLaunchKernelGGL(k_gram_reduce<false>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
+                           part, C, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
     return hipGetLastError();
 }
 
 hipError_t launch_spectrum_kernel_loss(int n, int Q, int lmax, const float* X, const float* Kref, float* Kt,
-                                       float* loss, float* scale, float* dX, hipStream_t stream)
+                                       float* loss, float* scale, float* dX, void* ws, hipStream_t stream)
 {
-    const int F = (lmax + 1) * Q * (Q + 1) / 2;
-    hipLaunchKernelGGL(k_gram, dim3(blocks_of(n, kT), blocks_of(n, kT)), dim3(256), 0, stream, n, F, Q, X, Kt);
-    hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, int64_t(n) * n, Kt, Kref, loss, scale);
-    hipLaunchKernelGGL(k_loss_grad, dim3(blocks_of(F, kT), blocks_of(n, kT)), dim3(256), 0, stream, n, F, Q, Kt, X,
-                       scale, dX);
+    const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
+    if (ws) {
+        // also with one slice: the tiles pass through the workspace so that
+        // the loss is summed by many work-groups
+        float* part = static_cast<float*>(ws);
+        double* sums = reinterpret_cast<double*>(part + size_t(g.slices) * g.tiles * 4096);
+        hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F,
+                           g.depth, Q, X, Kt, part);
+        hipLaunchKernelGGL(k_gram_reduce<true>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
+                           part, Kt, Kref, sums);
+        hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, 4 * g.tiles, sums, Kt, Kref, loss, scale);
+    } else {
+        hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X, Kt,
+                           static_cast<float*>(nullptr));
+        hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, int64_t(n) * n,
+                           static_cast<const double*>(nullptr), Kt, Kref, loss, scale);
+    }
+    hipLaunchKernelGGL(k_loss_grad, dim3(blocks_of(g.F, tf::kTile), blocks_of(n, tf::kTile)), dim3(256), 0, stream, n,
+                       g.F, Q, Kt, X, scale, dX);
     return hipGetLastError();
 }
 

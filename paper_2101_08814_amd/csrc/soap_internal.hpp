@@ -210,9 +210,11 @@ hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_backward(const CompressArgs& a, float* grad, hipStream_t stream);
 hipError_t launch_channel_cov(const CompressArgs& a, float* part, int slices, hipStream_t stream);
-hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C, hipStream_t stream);
+// ws: spectrum_gram_workspace() bytes, or NULL (one chain over the features)
+size_t spectrum_gram_workspace(int n, int Q, int lmax);
+hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C, void* ws, hipStream_t stream);
 hipError_t launch_spectrum_kernel_loss(int n, int Q, int lmax, const float* X, const float* Kref, float* Kt,
-                                       float* loss, float* scale, float* dX, hipStream_t stream);
+                                       float* loss, float* scale, float* dX, void* ws, hipStream_t stream);
 hipError_t launch_adam(int64_t n, float* p, const float* g, float* m, float* v, float lr, float b1, float b2,
                        float eps, int step, hipStream_t stream);
 

@@ -548,24 +548,33 @@ class Compressor:
                                                   _ptr(grad_p), _ptr(self._ws), self._ws.numel(), _ptr(out)))
         return out
 
+    def _gram_workspace(self, n: int, n_channels: int, dev) -> torch.Tensor:
+        nb = ctypes.c_size_t()
+        check(self.calc._L.soap_spectrum_gram_workspace_size(n, int(n_channels), self.lmax, ctypes.byref(nb)))
+        return torch.empty(max(int(nb.value), 1), dtype=torch.uint8, device=dev)
+
     def gram(self, X: torch.Tensor, n_channels: int) -> torch.Tensor:
-        """soap_spectrum_gram of packed spectra X [n, lmax+1, Q(Q+1)/2]."""
+        """soap_spectrum_gram_ws of packed spectra X [n, lmax+1, Q(Q+1)/2]."""
         assert X.dtype == torch.float32 and X.is_contiguous()
         n = int(X.shape[0])
         K = torch.empty((n, n), dtype=torch.float32, device=X.device)
+        ws = self._gram_workspace(n, n_channels, X.device)
         e = self.calc._exec()
-        check(self.calc._L.soap_spectrum_gram(ctypes.byref(e), n, int(n_channels), self.lmax, _ptr(X), _ptr(K)))
+        check(self.calc._L.soap_spectrum_gram_ws(ctypes.byref(e), n, int(n_channels), self.lmax, _ptr(X), _ptr(K),
+                                                 _ptr(ws), ws.numel()))
         return K
 
     def kernel_loss(self, X: torch.Tensor, Kref: torch.Tensor):
-        """soap_spectrum_kernel_loss for compressed spectra X: (loss as a
+        """soap_spectrum_kernel_loss_ws for compressed spectra X: (loss as a
         device tensor [1], dL/dX)."""
         n = int(X.shape[0])
         work = torch.empty(n * n + 1, dtype=torch.float32, device=X.device)
         gX = torch.empty_like(X)
+        ws = self._gram_workspace(n, self.Q, X.device)
         e = self.calc._exec()
-        check(self.calc._L.soap_spectrum_kernel_loss(ctypes.byref(e), n, self.Q, self.lmax, _ptr(X), _ptr(Kref),
-                                                     _ptr(work), _ptr(self._loss), _ptr(gX)))
+        check(self.calc._L.soap_spectrum_kernel_loss_ws(ctypes.byref(e), n, self.Q, self.lmax, _ptr(X), _ptr(Kref),
+                                                        _ptr(work), _ptr(self._loss), _ptr(gX), _ptr(ws),
+                                                        ws.numel()))
         return self._loss, gX
 
     def adam(self, lr: float, beta1: float = 0.9, beta2: float = 0.999, eps: float = 1e-8):
