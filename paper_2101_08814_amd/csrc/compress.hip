@@ -1288,6 +1288,8 @@ size_t compress_bwd_lds(const CompressArgs& a)
 hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream)
 {
     if (a.n == 0) return hipSuccess;
+    const hipError_t tiled = launch_train_forward(a, stream);
+    if (tiled != hipErrorNotSupported) return tiled;
     const size_t lds = compress_fwd_lds(a);
     if (lds > 160 * 1024) return hipErrorNotSupported;
     auto kernel = a.ct ? (a.pt ? k_cmp_fwd<true, true> : k_cmp_fwd<true, false>) : k_cmp_fwd<false, true>;
@@ -1371,6 +1373,8 @@ hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t strea
 
 hipError_t launch_compress_backward(const CompressArgs& a, float* grad, hipStream_t stream)
 {
+    const hipError_t tiled = launch_train_backward(a, grad, stream);
+    if (tiled != hipErrorNotSupported) return tiled;
     const size_t lds = compress_bwd_lds(a);
     if (lds > 160 * 1024) return hipErrorNotSupported;
     if (lds > 65536) {

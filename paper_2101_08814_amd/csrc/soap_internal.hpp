@@ -206,6 +206,10 @@ struct CompressArgs {
 size_t compress_image_bytes(int K, int Q, int H, int lmax);
 size_t compress_fwd_lds(const CompressArgs& a);
 size_t compress_bwd_lds(const CompressArgs& a);
+// float forward and backward on the matrix cores (compress_train.hip);
+// hipErrorNotSupported for K or H over 128 or Q over 32
+hipError_t launch_train_forward(const CompressArgs& a, hipStream_t stream);
+hipError_t launch_train_backward(const CompressArgs& a, float* grad, hipStream_t stream);
 hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_backward(const CompressArgs& a, float* grad, hipStream_t stream);
