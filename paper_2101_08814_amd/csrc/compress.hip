@@ -926,20 +926,39 @@ __device__ __forceinline__ unsigned int pack_bf16(float lo, float hi)
     return __builtin_bit_cast(unsigned int, __builtin_convertvector(v, bf16x2));
 }
 
-// sum over the 16 lanes of a DPP row (every lane receives the sum)
-__device__ __forceinline__ float row_sum16(float s)
+// exchanges between halves of a wave: lanes 32..63 of a with lanes 0..31 of
+// b, or odd rows of 16 lanes of a with the even rows of b; the sum leaves a's
+// total of lane pairs (32 or 16 apart) in the lower member and b's in the
+// upper one
+__device__ __forceinline__ float swap32_sum(float a, float b)
 {
-    s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x128, 0xF, 0xF, false));
-    s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x124, 0xF, 0xF, false));
-    s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x122, 0xF, 0xF, false));
-    s += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x121, 0xF, 0xF, false));
-    return s;
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_sum(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// out[k] = x of the lane's row k of 16 lanes, in every row
+__device__ __forceinline__ void gather_rows(float x, float (&out)[4])
+{
+    const unsigned u = __float_as_uint(x);
+    const auto e = __builtin_amdgcn_permlane16_swap(u, u, false, false);        // rows 0 0 2 2, rows 1 1 3 3
+    const auto p = __builtin_amdgcn_permlane32_swap(e[0], e[0], false, false);   // row 0, row 2
+    const auto q = __builtin_amdgcn_permlane32_swap(e[1], e[1], false, false);   // row 1, row 3
+    out[0] = __uint_as_float(p[0]);
+    out[1] = __uint_as_float(q[0]);
+    out[2] = __uint_as_float(p[1]);
+    out[3] = __uint_as_float(q[1]);
 }
 
 struct WaveLayout {
     int Kp, XS, Hp, HS, HT, KS, KS2, QT, cpw;
     int E1, E2, E;           // weight float4s per l: W1 rows, W2 rows, then {alpha, beta}
-    int x_bytes, cb_bytes;   // per centre
+    int x_bytes, cb_bytes;   // per centre (cb: the gated hidden columns, then c~)
+    int GS;                  // row stride of the gated hidden columns, in pairs of units
     int w1, w2, ab, x, cb, total;   // byte offsets, 16-byte aligned
     int wbytes;              // bytes of one l's weights in LDS
     int wstride;             // with the image: one l's image rounded up to whole 1 KB pieces (two LDS buffers)
@@ -965,7 +984,11 @@ __host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax,
     const int L2 = (lmax + 1) * (lmax + 1);
     // c of one l in FP32, [k][2l+1] rows, whole 64-element pieces
     W.x_bytes = up16(((K * (2 * lmax + 1) + 63) / 64) * 64 * 4);
-    W.cb_bytes = up16(W.QT * 16 * kCB * 4);
+    // rows [m][unit pair] of bfloat16: 4 GS mod 64 = 16 for Hp = 128, so that
+    // the 16 lanes of each row and the four rows of a store meet all banks
+    W.GS = W.Hp / 2 + 4;
+    const int gt = 16 * W.GS * 4, cb = W.QT * 16 * kCB * 4;
+    W.cb_bytes = up16(gt > cb ? gt : cb);
     int o = 0;
     W.w1 = o; o += up16(W.HT * 16 * W.XS * 2);
     W.w2 = o; o += up16(W.QT * 16 * W.HS * 2);
@@ -983,7 +1006,7 @@ __host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax,
 __device__ __forceinline__ int wave_unit(int row)
 {
     const int t = row >> 4, rho = row & 15;
-    return 32 * (t >> 1) + 8 * (rho >> 2) + 4 * (t & 1) + (rho & 3);
+    return 32 * (t >> 1) + 2 * rho + (t & 1);
 }
 
 // Weight float4 e of one l: its offset in the l's weights (-1: outside
@@ -1142,8 +1165,10 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         }
         if (!live) continue;
         const int M = 2 * l + 1, b = l * l, MT = (M + 15) >> 4;
-        // layer 1: k-steps outside, the hidden tiles' accumulators inside;
-        // each W1 fragment serves both column tiles as it is read
+        // layer 1, transposed (D rows m, columns hidden units): k-steps
+        // outside, the hidden tiles' accumulators inside; each W1 fragment
+        // serves both m tiles as it is read.  Lane (r, g) then holds units
+        // 32 (t / 2) + 2 r + (t & 1) of tile t at m = 16 ct + 4 g + v.
         f32x4 h[2][8];
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct)
@@ -1160,65 +1185,99 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
                     if (t < W.HT) {
                         const u16x8 A = *reinterpret_cast<const u16x8*>(&W1s[(16 * t + r) * W.XS + 32 * kk + 8 * g]);
                         h[0][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, B0), h[0][t], 0, 0, 0);
+                            __builtin_bit_cast(bf16x8, B0), __builtin_bit_cast(bf16x8, A), h[0][t], 0, 0, 0);
                         if (MT > 1)
                             h[1][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, A), __builtin_bit_cast(bf16x8, B1), h[1][t], 0, 0, 0);
+                                __builtin_bit_cast(bf16x8, B1), __builtin_bit_cast(bf16x8, A), h[1][t], 0, 0, 0);
                     }
                 }
             }
         }
         wave_sync();   // every read of X of l is done
         if (l < lmax) fetch_x(l + 1);
-        // gate factor 2 sigma(alpha |h| + beta) of unit q (row 4g + v of
-        // tile t), |h_q|^2 summed over the m columns (zero where not
-        // computed); h is scaled in place
-        for (int t = 0; t < 8; ++t) {
-            const int q0 = 32 * (t >> 1) + 8 * g + 4 * (t & 1);
-            const float4 al = *reinterpret_cast<const float4*>(ab + q0);
-            const float4 be = *reinterpret_cast<const float4*>(ab + W.Hp + q0);
-            const float alv[4] = {al.x, al.y, al.z, al.w}, bev[4] = {be.x, be.y, be.z, be.w};
+        // |h|^2 over m, added as a tree: m and m + 8 (lanes 32 apart), m + 4
+        // (16 apart), m + 2 and m + 1 (in the lane).  Each exchange halves the
+        // tiles a lane answers for, so that lane (r, g) ends with units
+        // 32 g + 2 r and 32 g + 2 r + 1 and every gate 2 sigma(alpha |h| +
+        // beta) is formed once in the wave (with the units in the rows every
+        // one of the 16 column lanes formed all of its row's: 650 of the
+        // 1,190 VALU instructions per degree).
+        float gate[8];
+        {
+            float s8[4][4], s4[2][4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float s = row_sum16(h[0][t][v] * h[0][t][v] + h[1][t][v] * h[1][t][v]);
-                const float x = alv[v] * __builtin_amdgcn_sqrtf(s) + bev[v];
-                const float G = (t < W.HT && q0 + v < H)
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float lo = h[0][t][v] * h[0][t][v] + h[1][t][v] * h[1][t][v];
+                    const float hi = h[0][t + 4][v] * h[0][t + 4][v] + h[1][t + 4][v] * h[1][t + 4][v];
+                    s8[t][v] = swap32_sum(lo, hi);
+                }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t + 2][v]);
+            const int q0 = 32 * g + 2 * r;
+            const int qs = q0 < H ? q0 : 0;   // H is a multiple of 4
+            const float2 al = *reinterpret_cast<const float2*>(ab + qs);
+            const float2 be = *reinterpret_cast<const float2*>(ab + W.Hp + qs);
+            const float alv[2] = {al.x, al.y}, bev[2] = {be.x, be.y};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float s = (s4[t][0] + s4[t][2]) + (s4[t][1] + s4[t][3]);
+                const float x = alv[t] * __builtin_amdgcn_sqrtf(s) + bev[t];
+                const float G = q0 < H
                                     ? 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x))
                                     : 0.0f;
-                h[0][t][v] *= G;
-                h[1][t][v] *= G;
+                float rows[4];
+                gather_rows(G, rows);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gate[2 * k + t] = rows[k];
             }
         }
-        // layer 2: c~ of the m columns -> the wave's staging (and c~ out)
+        // the gated columns as bfloat16 pairs of units, rows m in the wave's
+        // staging, and layer 2 on them: c~ of the m columns
+        unsigned int* gt = reinterpret_cast<unsigned int*>(cb);
+        f32x4 acc2[2][QT];
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct) {
             if (ct >= MT) continue;
-            f32x4 acc2[QT];
+            wave_sync();
 #pragma unroll
-            for (int pt = 0; pt < QT; ++pt) acc2[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < 4; ++u) {
+                if (u >= W.KS2) continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    gt[(4 * g + v) * W.GS + 16 * u + r] =
+                        pack_bf16(h[ct][2 * u][v] * gate[2 * u], h[ct][2 * u + 1][v] * gate[2 * u + 1]);
+            }
+            wave_sync();
+#pragma unroll
+            for (int pt = 0; pt < QT; ++pt) acc2[ct][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 if (ks >= W.KS2) continue;
-                u32x4 Bw;
-                Bw[0] = pack_bf16(h[ct][2 * ks][0], h[ct][2 * ks][1]);
-                Bw[1] = pack_bf16(h[ct][2 * ks][2], h[ct][2 * ks][3]);
-                Bw[2] = pack_bf16(h[ct][2 * ks + 1][0], h[ct][2 * ks + 1][1]);
-                Bw[3] = pack_bf16(h[ct][2 * ks + 1][2], h[ct][2 * ks + 1][3]);
+                const u32x4 Bw = *reinterpret_cast<const u32x4*>(gt + r * W.GS + 16 * ks + 4 * g);
 #pragma unroll
                 for (int pt = 0; pt < QT; ++pt) {
                     const u16x8 A2 = *reinterpret_cast<const u16x8*>(&W2s[(16 * pt + r) * W.HS + 32 * ks + 8 * g]);
-                    acc2[pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A2),
-                                                                       __builtin_bit_cast(bf16x8, Bw), acc2[pt], 0, 0, 0);
+                    acc2[ct][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, A2), __builtin_bit_cast(bf16x8, Bw), acc2[ct][pt], 0, 0, 0);
                 }
             }
+        }
+        wave_sync();   // c~ goes over the gated columns
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+            if (ct >= MT) continue;
             const int m = 16 * ct + r;
 #pragma unroll
             for (int pt = 0; pt < QT; ++pt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int p = 16 * pt + 4 * g + v;
-                    cb[p * kCB + m] = acc2[pt][v];
-                    if (WANT_CT && p < Q && m < M) a.ct[(i * Q + p) * int64_t(L2) + b + m] = acc2[pt][v];
+                    cb[p * kCB + m] = acc2[ct][pt][v];
+                    if (WANT_CT && p < Q && m < M) a.ct[(i * Q + p) * int64_t(L2) + b + m] = acc2[ct][pt][v];
                 }
         }
         if (WANT_PT) {
