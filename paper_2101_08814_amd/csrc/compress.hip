@@ -18,6 +18,7 @@
 // full symmetric spectrum (packed off-diagonal entries weighted 2):
 //   L = |K~ - K|_F^2 / |K|_F^2.
 #include <cmath>
+#include <type_traits>
 
 #include "chunk.hpp"
 #include "tile_f32.hpp"
@@ -971,7 +972,7 @@ __host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax,
     WaveLayout W;
     W.Kp = (K + 31) / 32 * 32;
     W.XS = W.Kp + 8;   // row stride (bf16) of W1: 16 consecutive rows hit distinct banks
-    W.Hp = (H + 31) / 32 * 32;
+    W.Hp = H <= 64 ? 64 : 128;   // four or eight hidden tiles
     W.HS = W.Hp + 8;
     W.HT = W.Hp / 16;
     W.KS = W.Kp / 32;
@@ -1061,26 +1062,34 @@ __global__ void __launch_bounds__(256) k_cmp_image(CompressArgs a, WaveLayout W)
 }
 
 
-// the layer-1 operand of column m: X[k0 + j][m], j < 8, as bfloat16 (zero
-// for k >= K), from the FP32 rows [k][w] of one l
+// the layer-1 operand of column m: X[k0 + j][m], j < 8, as bfloat16 (with
+// CHECK zero for k >= K), from the FP32 rows [k][w] of one l
+template <bool CHECK>
 __device__ __forceinline__ u16x8 x_operand(const float* Xf, int w, int m, int k0, int K)
 {
     float x[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = k0 + j < K ? Xf[(k0 + j) * w + m] : 0.0f;
+    for (int j = 0; j < 8; ++j) x[j] = !CHECK || k0 + j < K ? Xf[(k0 + j) * w + m] : 0.0f;
     u32x4 p;
 #pragma unroll
     for (int j = 0; j < 4; ++j) p[j] = pack_bf16(x[2 * j], x[2 * j + 1]);
     return __builtin_bit_cast(u16x8, p);
 }
 
-template <bool WANT_CT, bool WANT_PT, int QT, bool IMG>
+// One wave per centre.  KS: 32-wide steps over the input channels; HT: tiles
+// of 16 hidden units (both compile-time, so that the weight reads of a
+// degree run ahead of their products: with a branch per tile every one of
+// the 24 LDS reads of layer 1 was waited for alone, 3.48 ms for 131,072
+// centres of 96 -> 128 -> 16 channels).
+template <int QT, bool IMG, int KS, int HT>
 __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs a, WaveLayout W)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int KS2 = HT / 2;
     const int K = a.K, Q = a.Q, H = a.H, lmax = a.lmax, L2 = (lmax + 1) * (lmax + 1);
     const int QQ = Q * (Q + 1) / 2;
-    const int tid = threadIdx.x, nthr = blockDim.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t i = int64_t(blockIdx.x) * W.cpw + wave;
     const bool live = i < a.n;
     const unsigned short* W1s = reinterpret_cast<const unsigned short*>(smem_raw + W.w1);
@@ -1118,79 +1127,69 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
     // c of degree l of this centre into the wave's X, FP32 rows [k][2l+1],
     // straight from global memory to LDS (64 elements per instruction; the
     // lanes past the end of the last piece read the first element and write
-    // the piece's tail, which nothing reads), issued one l ahead
+    // the piece's tail, which nothing reads), issued one l ahead.  A lane's
+    // element moves on by 64 = a (2l+1) + b each time.
     const float* cc = a.c + (live ? i : 0) * int64_t(K) * L2;
     auto fetch_x = [&](int l) __attribute__((always_inline)) {
         const int w = 2 * l + 1, n = K * w;
-        const float inv = 1.0f / float(w);
+        const float* cl = cc + l * l;
+        const int k0 = int((float(lane) + 0.5f) * (1.0f / float(w)));
+        int m = lane - k0 * w;
+        const int da = 64 / w, dm = 64 - da * w;
+        unsigned off = unsigned(k0 * L2 + m) * 4u;
+        const unsigned step = unsigned(da * L2 + dm) * 4u, wrap = unsigned(L2 - w) * 4u;
         for (int e0 = 0; e0 < n; e0 += 64) {
-            const int e = e0 + lane < n ? e0 + lane : 0;
-            const int k = int((float(e) + 0.5f) * inv), m = e - k * w;
-            __builtin_amdgcn_global_load_lds(cc + k * L2 + l * l + m,
+            const unsigned o = e0 + lane < n ? off : 0u;
+            __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(cl) + o,
                                              (__attribute__((address_space(3))) void*)(Xf + e0), 4, 0, 0);
+            m += dm;
+            off += step;
+            if (m >= w) {
+                m -= w;
+                off += wrap;
+            }
         }
     };
     if (live) fetch_x(0);
 
-    const float* wl = a.w;
-    for (int l = 0; l <= lmax; ++l, wl += lsize) {
-        __syncthreads();   // the weights of l - 1 are no longer read
-        if constexpr (IMG) {
-            // l's image is in buffer l % 2 once every wave's loads are done;
-            // buffer (l + 1) % 2 held l - 1, which no wave reads any more
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            if (l < lmax) fetch_image(l + 1);
-            const unsigned char* wb = smem_raw + (l & 1) * W.wstride;
-            W1s = reinterpret_cast<const unsigned short*>(wb + W.w1);
-            W2s = reinterpret_cast<const unsigned short*>(wb + W.w2);
-            ab = reinterpret_cast<const float*>(wb + W.ab);
-        } else {
-            __builtin_amdgcn_s_waitcnt(0);   // this wave's X of l
-            float4 wv[kWQuads];
-#pragma unroll
-            for (int u = 0; u < kWQuads; ++u)   // every load issued before any is used
-                wv[u] = *reinterpret_cast<const float4*>(wl + (wsrc[u] >= 0 ? wsrc[u] : 0));
-#pragma unroll
-            for (int u = 0; u < kWQuads; ++u)
-                if (wdst[u] >= 0)
-                    wave_weight_put(smem_raw, W, wdst[u], wsrc[u] >= 0 ? wv[u] : make_float4(0.f, 0.f, 0.f, 0.f));
-            for (int e = tid + nthr * kWQuads; e < W.E; e += nthr) {   // beyond the kept offsets
-                int s0, d0;
-                wave_weight_slot(a, W, e, s0, d0);
-                wave_weight_put(smem_raw, W, d0,
-                                s0 >= 0 ? *reinterpret_cast<const float4*>(wl + s0) : make_float4(0.f, 0.f, 0.f, 0.f));
-            }
-            __syncthreads();
-        }
-        if (!live) continue;
-        const int M = 2 * l + 1, b = l * l, MT = (M + 15) >> 4;
+    // packed positions of this lane's outputs of tile (0, 0): row 4 g + v,
+    // column r; -1 below the diagonal or past Q
+    auto packed = [&](int P1, int P2, int v) __attribute__((always_inline)) {
+        const int p1 = 16 * P1 + 4 * g + v, p2 = 16 * P2 + r;
+        return p1 <= p2 && p2 < Q ? p1 * Q - p1 * (p1 - 1) / 2 + (p2 - p1) : -1;
+    };
+
+    // one degree with MT tiles of 16 columns m
+    auto degree = [&](auto mt, int l) __attribute__((always_inline)) {
+        constexpr int MT = decltype(mt)::value;
+        const int M = 2 * l + 1, b = l * l;
         // layer 1, transposed (D rows m, columns hidden units): k-steps
         // outside, the hidden tiles' accumulators inside; each W1 fragment
-        // serves both m tiles as it is read.  Lane (r, g) then holds units
+        // serves every m tile as it is read.  Lane (r, g) then holds units
         // 32 (t / 2) + 2 r + (t & 1) of tile t at m = 16 ct + 4 g + v.
-        f32x4 h[2][8];
+        f32x4 h[MT][HT];
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int ct = 0; ct < MT; ++ct)
 #pragma unroll
-            for (int t = 0; t < 8; ++t) h[ct][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < HT; ++t) h[ct][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            if (kk < W.KS) {
-                u16x8 B0 = u16x8{0, 0, 0, 0, 0, 0, 0, 0}, B1 = B0;
-                if (r < M) B0 = x_operand(Xf, M, r, 32 * kk + 8 * g, K);
-                if (16 + r < M) B1 = x_operand(Xf, M, 16 + r, 32 * kk + 8 * g, K);
+        for (int kk = 0; kk < KS; ++kk) {
+            u16x8 B[MT];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if (t < W.HT) {
-                        const u16x8 A = *reinterpret_cast<const u16x8*>(&W1s[(16 * t + r) * W.XS + 32 * kk + 8 * g]);
-                        h[0][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            __builtin_bit_cast(bf16x8, B0), __builtin_bit_cast(bf16x8, A), h[0][t], 0, 0, 0);
-                        if (MT > 1)
-                            h[1][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, B1), __builtin_bit_cast(bf16x8, A), h[1][t], 0, 0, 0);
-                    }
+            for (int ct = 0; ct < MT; ++ct) {
+                B[ct] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};
+                if (16 * ct + r < M) {
+                    if (kk < KS - 1) B[ct] = x_operand<false>(Xf, M, 16 * ct + r, 32 * kk + 8 * g, K);
+                    else B[ct] = x_operand<true>(Xf, M, 16 * ct + r, 32 * kk + 8 * g, K);
                 }
+            }
+#pragma unroll
+            for (int t = 0; t < HT; ++t) {
+                const u16x8 A = *reinterpret_cast<const u16x8*>(&W1s[(16 * t + r) * W.XS + 32 * kk + 8 * g]);
+#pragma unroll
+                for (int ct = 0; ct < MT; ++ct)
+                    h[ct][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, B[ct]), __builtin_bit_cast(bf16x8, A), h[ct][t], 0, 0, 0);
             }
         }
         wave_sync();   // every read of X of l is done
@@ -1198,26 +1197,42 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         // |h|^2 over m, added as a tree: m and m + 8 (lanes 32 apart), m + 4
         // (16 apart), m + 2 and m + 1 (in the lane).  Each exchange halves the
         // tiles a lane answers for, so that lane (r, g) ends with units
-        // 32 g + 2 r and 32 g + 2 r + 1 and every gate 2 sigma(alpha |h| +
+        // 32 g + 2 r and 32 g + 2 r + 1 (of 64 units: every two rows of 16
+        // lanes alike, 32 (g / 2) + 2 r) and every gate 2 sigma(alpha |h| +
         // beta) is formed once in the wave (with the units in the rows every
         // one of the 16 column lanes formed all of its row's: 650 of the
-        // 1,190 VALU instructions per degree).
-        float gate[8];
+        // 1,190 VALU instructions per degree, 4.40 ms).
+        float gate[HT];
         {
-            float s8[4][4], s4[2][4];
+            auto square = [&](int t, int v) __attribute__((always_inline)) {
+                if constexpr (MT == 2) return h[0][t][v] * h[0][t][v] + h[MT - 1][t][v] * h[MT - 1][t][v];
+                else return h[0][t][v] * h[0][t][v];
+            };
+            float s4[2][4];
+            int q0;
+            if constexpr (HT == 8) {
+                float s8[4][4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float lo = h[0][t][v] * h[0][t][v] + h[1][t][v] * h[1][t][v];
-                    const float hi = h[0][t + 4][v] * h[0][t + 4][v] + h[1][t + 4][v] * h[1][t + 4][v];
-                    s8[t][v] = swap32_sum(lo, hi);
-                }
+                    for (int v = 0; v < 4; ++v) s8[t][v] = swap32_sum(square(t, v), square(t + 4, v));
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t + 2][v]);
-            const int q0 = 32 * g + 2 * r;
+                    for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t + 2][v]);
+                q0 = 32 * g + 2 * r;
+            } else {
+                float s8[2][4];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s8[t][v] = swap32_sum(square(t, v), square(t + 2, v));
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t][v]);
+                q0 = 32 * (g >> 1) + 2 * r;
+            }
             const int qs = q0 < H ? q0 : 0;   // H is a multiple of 4
             const float2 al = *reinterpret_cast<const float2*>(ab + qs);
             const float2 be = *reinterpret_cast<const float2*>(ab + W.Hp + qs);
@@ -1232,31 +1247,27 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
                 float rows[4];
                 gather_rows(G, rows);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) gate[2 * k + t] = rows[k];
+                for (int k = 0; k < HT / 2; ++k) gate[2 * k + t] = rows[HT == 8 ? k : 2 * k];
             }
         }
         // the gated columns as bfloat16 pairs of units, rows m in the wave's
         // staging, and layer 2 on them: c~ of the m columns
         unsigned int* gt = reinterpret_cast<unsigned int*>(cb);
-        f32x4 acc2[2][QT];
+        f32x4 acc2[MT][QT];
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            if (ct >= MT) continue;
+        for (int ct = 0; ct < MT; ++ct) {
             wave_sync();
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (u >= W.KS2) continue;
+            for (int u = 0; u < KS2; ++u)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     gt[(4 * g + v) * W.GS + 16 * u + r] =
                         pack_bf16(h[ct][2 * u][v] * gate[2 * u], h[ct][2 * u + 1][v] * gate[2 * u + 1]);
-            }
             wave_sync();
 #pragma unroll
             for (int pt = 0; pt < QT; ++pt) acc2[ct][pt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if (ks >= W.KS2) continue;
+            for (int ks = 0; ks < KS2; ++ks) {
                 const u32x4 Bw = *reinterpret_cast<const u32x4*>(gt + r * W.GS + 16 * ks + 4 * g);
 #pragma unroll
                 for (int pt = 0; pt < QT; ++pt) {
@@ -1268,8 +1279,7 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         }
         wave_sync();   // c~ goes over the gated columns
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            if (ct >= MT) continue;
+        for (int ct = 0; ct < MT; ++ct) {
             const int m = 16 * ct + r;
 #pragma unroll
             for (int pt = 0; pt < QT; ++pt)
@@ -1277,10 +1287,10 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
                 for (int v = 0; v < 4; ++v) {
                     const int p = 16 * pt + 4 * g + v;
                     cb[p * kCB + m] = acc2[ct][pt][v];
-                    if (WANT_CT && p < Q && m < M) a.ct[(i * Q + p) * int64_t(L2) + b + m] = acc2[ct][pt][v];
+                    if (a.ct && p < Q && m < M) a.ct[(i * Q + p) * int64_t(L2) + b + m] = acc2[ct][pt][v];
                 }
         }
-        if (WANT_PT) {
+        if (a.pt) {
             wave_sync();
             // rows 16 P + r of c~ as the lane's operand: m = 8 g + j, zero past
             // the columns written for this l; high and low bfloat16 parts
@@ -1314,15 +1324,50 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lo[P1]),
                                                                   __builtin_bit_cast(bf16x8, hi[P2]), acc, 0, 0, 0);
                     // lane holds p~[p1][p2], p1 = 16 P1 + 4 g + v, p2 = 16 P2 + r
-                    const int p2 = 16 * P2 + r;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int p1 = 16 * P1 + 4 * g + v;
-                        if (p1 <= p2 && p2 < Q) dst[p1 * Q - p1 * (p1 - 1) / 2 + (p2 - p1)] = acc[v];
+                        const int at = packed(P1, P2, v);
+                        if (at >= 0) dst[at] = acc[v];
                     }
                 }
             wave_sync();
         }
+    };
+
+    const float* wl = a.w;
+    for (int l = 0; l <= lmax; ++l, wl += lsize) {
+        __syncthreads();   // the weights of l - 1 are no longer read
+        if constexpr (IMG) {
+            // l's image is in buffer l % 2 once every wave's loads are done;
+            // buffer (l + 1) % 2 held l - 1, which no wave reads any more
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (l < lmax) fetch_image(l + 1);
+            const unsigned char* wb = smem_raw + (l & 1) * W.wstride;
+            W1s = reinterpret_cast<const unsigned short*>(wb + W.w1);
+            W2s = reinterpret_cast<const unsigned short*>(wb + W.w2);
+            ab = reinterpret_cast<const float*>(wb + W.ab);
+        } else {
+            __builtin_amdgcn_s_waitcnt(0);   // this wave's X of l
+            float4 wv[kWQuads];
+#pragma unroll
+            for (int u = 0; u < kWQuads; ++u)   // every load issued before any is used
+                wv[u] = *reinterpret_cast<const float4*>(wl + (wsrc[u] >= 0 ? wsrc[u] : 0));
+#pragma unroll
+            for (int u = 0; u < kWQuads; ++u)
+                if (wdst[u] >= 0)
+                    wave_weight_put(smem_raw, W, wdst[u], wsrc[u] >= 0 ? wv[u] : make_float4(0.f, 0.f, 0.f, 0.f));
+            for (int e = tid + nthr * kWQuads; e < W.E; e += nthr) {   // beyond the kept offsets
+                int s0, d0;
+                wave_weight_slot(a, W, e, s0, d0);
+                wave_weight_put(smem_raw, W, d0,
+                                s0 >= 0 ? *reinterpret_cast<const float4*>(wl + s0) : make_float4(0.f, 0.f, 0.f, 0.f));
+            }
+            __syncthreads();
+        }
+        if (!live) continue;
+        if (l < 8) degree(std::integral_constant<int, 1>{}, l);
+        else degree(std::integral_constant<int, 2>{}, l);
     }
 }
 
@@ -1362,6 +1407,25 @@ hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream)
 }
 
 
+template <int QT, bool IMG, int KS, int HT>
+hipError_t launch_cmp_wave_t(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
+{
+    auto kernel = k_cmp_fwd_wave<QT, IMG, KS, HT>;
+    if (W.total > 65536) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, W.total);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(blocks_of(a.n, W.cpw)), dim3(64 * W.cpw), size_t(W.total), stream, a, W);
+    return hipGetLastError();
+}
+
+template <int QT, bool IMG, int KS>
+hipError_t launch_cmp_wave_h(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
+{
+    return W.HT == 4 ? launch_cmp_wave_t<QT, IMG, KS, 4>(a, W, stream) : launch_cmp_wave_t<QT, IMG, KS, 8>(a, W, stream);
+}
+
 template <int QT, bool IMG>
 hipError_t launch_cmp_wave_q(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
 {
@@ -1370,15 +1434,10 @@ hipError_t launch_cmp_wave_q(const CompressArgs& a, const WaveLayout& W, hipStre
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    auto kernel = a.ct ? (a.pt ? k_cmp_fwd_wave<true, true, QT, IMG> : k_cmp_fwd_wave<true, false, QT, IMG>)
-                       : k_cmp_fwd_wave<false, true, QT, IMG>;
-    if (W.total > 65536) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, W.total);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, dim3(blocks_of(a.n, W.cpw)), dim3(64 * W.cpw), size_t(W.total), stream, a, W);
-    return hipGetLastError();
+    return W.KS == 1   ? launch_cmp_wave_h<QT, IMG, 1>(a, W, stream)
+           : W.KS == 2 ? launch_cmp_wave_h<QT, IMG, 2>(a, W, stream)
+           : W.KS == 3 ? launch_cmp_wave_h<QT, IMG, 3>(a, W, stream)
+                       : launch_cmp_wave_h<QT, IMG, 4>(a, W, stream);
 }
 
 // the one-wave-per-centre form when the shapes fit it: K, H <= 128 and
