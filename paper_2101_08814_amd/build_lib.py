@@ -17,7 +17,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsoap_mi355x.so")
 
 SOURCES = ["capi.cpp", "tables.cpp", "neighbors.hip", "features.hip", "gradient_rows.hip", "power_spectrum.hip",
-           "backward.hip", "compress.hip", "compress_train.hip", "gpr.hip", "selected.hip", "noalloc.hip",
+           "backward.hip", "compress.hip", "compress_train.hip", "compress_infer.hip", "gpr.hip", "selected.hip", "noalloc.hip",
            "expansion_lanes.hip", "expansion_packed.hip", "backward_lanes.hip",
            "radial.hip", "features_rows.hip"]
 

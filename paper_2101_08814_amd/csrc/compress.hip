@@ -21,12 +21,14 @@
 #include <type_traits>
 
 #include "chunk.hpp"
+#include "compress_bf16.hpp"
 #include "tile_f32.hpp"
 
 namespace soap {
 namespace {
 
 using namespace dev;
+using namespace cmp;
 
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
 
@@ -543,9 +545,6 @@ constexpr int kMT = 4;         // hidden tiles per wave (H <= 256)
 constexpr int kKS1 = 4;        // k-steps of the first layer (K <= 128)
 constexpr int kKS2 = 8;        // k-steps of the second layer (H <= 256)
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ unsigned short to_bf16(float f)
 {
@@ -913,47 +912,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_cmp_fwd_bf16_r(CompressArgs a)
 //            full spectrum), from c~ staged in the wave's own LDS.
 // Two work-group barriers per l (the shared weights); none per m.
 constexpr int kWaveCentres = 8;   // most centres (waves) per work-group
-constexpr int kCB = 36;           // row stride of the c~ staging (floats, 16-byte rows)
 constexpr int kWQuads = 12;       // weight float4s a lane stages per l from kept offsets
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// two floats to packed bfloat16 (round to nearest even), low half first
-__device__ __forceinline__ unsigned int pack_bf16(float lo, float hi)
-{
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(unsigned int, __builtin_convertvector(v, bf16x2));
-}
-
-// exchanges between halves of a wave: lanes 32..63 of a with lanes 0..31 of
-// b, or odd rows of 16 lanes of a with the even rows of b; the sum leaves a's
-// total of lane pairs (32 or 16 apart) in the lower member and b's in the
-// upper one
-__device__ __forceinline__ float swap32_sum(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float swap16_sum(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// out[k] = x of the lane's row k of 16 lanes, in every row
-__device__ __forceinline__ void gather_rows(float x, float (&out)[4])
-{
-    const unsigned u = __float_as_uint(x);
-    const auto e = __builtin_amdgcn_permlane16_swap(u, u, false, false);        // rows 0 0 2 2, rows 1 1 3 3
-    const auto p = __builtin_amdgcn_permlane32_swap(e[0], e[0], false, false);   // row 0, row 2
-    const auto q = __builtin_amdgcn_permlane32_swap(e[1], e[1], false, false);   // row 1, row 3
-    out[0] = __uint_as_float(p[0]);
-    out[1] = __uint_as_float(q[0]);
-    out[2] = __uint_as_float(p[1]);
-    out[3] = __uint_as_float(q[1]);
-}
 
 struct WaveLayout {
     int Kp, XS, Hp, HS, HT, KS, KS2, QT, cpw;
@@ -961,13 +920,11 @@ struct WaveLayout {
     int x_bytes, cb_bytes;   // per centre (cb: the gated hidden columns, then c~)
     int GS;                  // row stride of the gated hidden columns, in pairs of units
     int w1, w2, ab, x, cb, total;   // byte offsets, 16-byte aligned
-    int wbytes;              // bytes of one l's weights in LDS
-    int wstride;             // with the image: one l's image rounded up to whole 1 KB pieces (two LDS buffers)
 };
 
 __host__ __device__ inline int up16(int b) { return (b + 15) & ~15; }
 
-__host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax, int cpw, bool img = false)
+__host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax, int cpw)
 {
     WaveLayout W;
     W.Kp = (K + 31) / 32 * 32;
@@ -994,20 +951,10 @@ __host__ __device__ inline WaveLayout wave_layout(int K, int Q, int H, int lmax,
     W.w1 = o; o += up16(W.HT * 16 * W.XS * 2);
     W.w2 = o; o += up16(W.QT * 16 * W.HS * 2);
     W.ab = o; o += up16(2 * W.Hp * 4);
-    W.wbytes = o;
-    W.wstride = (o + 1023) & ~1023;
-    if (img) o = 2 * W.wstride;
     W.x = o; o += cpw * W.x_bytes;
     W.cb = o; o += cpw * W.cb_bytes;
     W.total = o;
     return W;
-}
-
-// hidden unit held by LDS row `row` of the staged W1
-__device__ __forceinline__ int wave_unit(int row)
-{
-    const int t = row >> 4, rho = row & 15;
-    return 32 * (t >> 1) + 2 * rho + (t & 1);
 }
 
 // Weight float4 e of one l: its offset in the l's weights (-1: outside
@@ -1017,7 +964,7 @@ __device__ __forceinline__ void wave_weight_slot(const CompressArgs& a, const Wa
 {
     const int K = a.K, H = a.H, Q = a.Q;
     if (e < W.E1) {
-        const int kq = W.Kp / 4, row = e / kq, k = 4 * (e - row * kq), q = wave_unit(row);
+        const int kq = W.Kp / 4, row = e / kq, k = 4 * (e - row * kq), q = hidden_unit(row >> 4, row & 15);
         src = (q < H && k < K) ? q * K + k : -1;
         dst = W.w1 + 2 * (row * W.XS + k);
     } else if (e < W.E1 + W.E2) {
@@ -1043,25 +990,6 @@ __device__ __forceinline__ void wave_weight_put(unsigned char* smem, const WaveL
     }
 }
 
-// The weights of every l as they sit in LDS (bfloat16 rows of W1 in the
-// unit order, W2 rows, then {alpha, beta} in float, zeros elsewhere): one
-// work-group per l writes bytes [0, W.x) of image l.
-__global__ void __launch_bounds__(256) k_cmp_image(CompressArgs a, WaveLayout W)
-{
-    const int l = blockIdx.x;
-    unsigned char* img = static_cast<unsigned char*>(a.img) + size_t(l) * W.wstride;
-    const float* wl = a.w + size_t(l) * (a.H * a.K + a.Q * a.H + 2 * a.H);
-    for (int e = threadIdx.x; e < W.wstride / 16; e += blockDim.x)
-        reinterpret_cast<uint4*>(img)[e] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < W.E; e += blockDim.x) {
-        int src, dst;
-        wave_weight_slot(a, W, e, src, dst);
-        wave_weight_put(img, W, dst, src >= 0 ? *reinterpret_cast<const float4*>(wl + src) : make_float4(0.f, 0.f, 0.f, 0.f));
-    }
-}
-
-
 // the layer-1 operand of column m: X[k0 + j][m], j < 8, as bfloat16 (with
 // CHECK zero for k >= K), from the FP32 rows [k][w] of one l
 template <bool CHECK>
@@ -1081,7 +1009,7 @@ __device__ __forceinline__ u16x8 x_operand(const float* Xf, int w, int m, int k0
 // degree run ahead of their products: with a branch per tile every one of
 // the 24 LDS reads of layer 1 was waited for alone, 3.48 ms for 131,072
 // centres of 96 -> 128 -> 16 channels).
-template <int QT, bool IMG, int KS, int HT>
+template <int QT, int KS, int HT>
 __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs a, WaveLayout W)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1094,36 +1022,20 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
     const bool live = i < a.n;
     const unsigned short* W1s = reinterpret_cast<const unsigned short*>(smem_raw + W.w1);
     const unsigned short* W2s = reinterpret_cast<const unsigned short*>(smem_raw + W.w2);
-    const float* ab = reinterpret_cast<const float*>(smem_raw + W.ab);   // (buffer l % 2 with the image)
+    const float* ab = reinterpret_cast<const float*>(smem_raw + W.ab);
     float* Xf = reinterpret_cast<float*>(smem_raw + W.x + wave * W.x_bytes);
     float* cb = reinterpret_cast<float*>(smem_raw + W.cb + wave * W.cb_bytes);
     const int lsize = H * K + Q * H + 2 * H;
 
     // this lane's weight float4s (the same offsets for every l)
-    int wsrc[IMG ? 1 : kWQuads], wdst[IMG ? 1 : kWQuads];
-    if constexpr (!IMG) {
+    int wsrc[kWQuads], wdst[kWQuads];
 #pragma unroll
-        for (int u = 0; u < kWQuads; ++u) {
-            const int e = tid + nthr * u;
-            wsrc[u] = -1;
-            wdst[u] = -1;
-            if (e < W.E) wave_weight_slot(a, W, e, wsrc[u], wdst[u]);
-        }
+    for (int u = 0; u < kWQuads; ++u) {
+        const int e = tid + nthr * u;
+        wsrc[u] = -1;
+        wdst[u] = -1;
+        if (e < W.E) wave_weight_slot(a, W, e, wsrc[u], wdst[u]);
     }
-    // with the image: l's weights go straight from global memory to LDS
-    // buffer l % 2 (16 bytes per lane, 1 KB per wave and instruction), the
-    // next l's while the current one is computed
-    const int nwaves = nthr >> 6;
-    auto fetch_image = [&](int l) __attribute__((always_inline)) {
-        const unsigned char* src = static_cast<const unsigned char*>(a.img) + size_t(l) * W.wstride;
-        unsigned char* dst = smem_raw + (l & 1) * W.wstride;
-        for (int piece = wave; piece < W.wstride / 1024; piece += nwaves)
-            __builtin_amdgcn_global_load_lds(src + piece * 1024 + lane * 16,
-                                             (__attribute__((address_space(3))) void*)(dst + piece * 1024),
-                                             16, 0, 0);
-    };
-    if constexpr (IMG) fetch_image(0);
-
     // c of degree l of this centre into the wave's X, FP32 rows [k][2l+1],
     // straight from global memory to LDS (64 elements per instruction; the
     // lanes past the end of the last piece read the first element and write
@@ -1151,13 +1063,6 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         }
     };
     if (live) fetch_x(0);
-
-    // packed positions of this lane's outputs of tile (0, 0): row 4 g + v,
-    // column r; -1 below the diagonal or past Q
-    auto packed = [&](int P1, int P2, int v) __attribute__((always_inline)) {
-        const int p1 = 16 * P1 + 4 * g + v, p2 = 16 * P2 + r;
-        return p1 <= p2 && p2 < Q ? p1 * Q - p1 * (p1 - 1) / 2 + (p2 - p1) : -1;
-    };
 
     // one degree with MT tiles of 16 columns m
     auto degree = [&](auto mt, int l) __attribute__((always_inline)) {
@@ -1194,62 +1099,10 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         }
         wave_sync();   // every read of X of l is done
         if (l < lmax) fetch_x(l + 1);
-        // |h|^2 over m, added as a tree: m and m + 8 (lanes 32 apart), m + 4
-        // (16 apart), m + 2 and m + 1 (in the lane).  Each exchange halves the
-        // tiles a lane answers for, so that lane (r, g) ends with units
-        // 32 g + 2 r and 32 g + 2 r + 1 (of 64 units: every two rows of 16
-        // lanes alike, 32 (g / 2) + 2 r) and every gate 2 sigma(alpha |h| +
-        // beta) is formed once in the wave (with the units in the rows every
-        // one of the 16 column lanes formed all of its row's: 650 of the
-        // 1,190 VALU instructions per degree, 4.40 ms).
+        const int q0 = gate_unit<HT>(r, g), qs = q0 < H ? q0 : 0;   // H is a multiple of 4
         float gate[HT];
-        {
-            auto square = [&](int t, int v) __attribute__((always_inline)) {
-                if constexpr (MT == 2) return h[0][t][v] * h[0][t][v] + h[MT - 1][t][v] * h[MT - 1][t][v];
-                else return h[0][t][v] * h[0][t][v];
-            };
-            float s4[2][4];
-            int q0;
-            if constexpr (HT == 8) {
-                float s8[4][4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) s8[t][v] = swap32_sum(square(t, v), square(t + 4, v));
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t + 2][v]);
-                q0 = 32 * g + 2 * r;
-            } else {
-                float s8[2][4];
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) s8[t][v] = swap32_sum(square(t, v), square(t + 2, v));
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) s4[t][v] = swap16_sum(s8[t][v], s8[t][v]);
-                q0 = 32 * (g >> 1) + 2 * r;
-            }
-            const int qs = q0 < H ? q0 : 0;   // H is a multiple of 4
-            const float2 al = *reinterpret_cast<const float2*>(ab + qs);
-            const float2 be = *reinterpret_cast<const float2*>(ab + W.Hp + qs);
-            const float alv[2] = {al.x, al.y}, bev[2] = {be.x, be.y};
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const float s = (s4[t][0] + s4[t][2]) + (s4[t][1] + s4[t][3]);
-                const float x = alv[t] * __builtin_amdgcn_sqrtf(s) + bev[t];
-                const float G = q0 < H
-                                    ? 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x))
-                                    : 0.0f;
-                float rows[4];
-                gather_rows(G, rows);
-#pragma unroll
-                for (int k = 0; k < HT / 2; ++k) gate[2 * k + t] = rows[HT == 8 ? k : 2 * k];
-            }
-        }
+        gates<MT, HT>(h, *reinterpret_cast<const float2*>(ab + qs), *reinterpret_cast<const float2*>(ab + W.Hp + qs),
+                      q0 < H, gate);
         // the gated columns as bfloat16 pairs of units, rows m in the wave's
         // staging, and layer 2 on them: c~ of the m columns
         unsigned int* gt = reinterpret_cast<unsigned int*>(cb);
@@ -1292,44 +1145,7 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
         }
         if (a.pt) {
             wave_sync();
-            // rows 16 P + r of c~ as the lane's operand: m = 8 g + j, zero past
-            // the columns written for this l; high and low bfloat16 parts
-            u32x4 hi[QT], lo[QT];
-#pragma unroll
-            for (int P = 0; P < QT; ++P) {
-                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                if (8 * g < 16 * MT) {
-                    const float4 x0 = *reinterpret_cast<const float4*>(cb + (16 * P + r) * kCB + 8 * g);
-                    const float4 x1 = *reinterpret_cast<const float4*>(cb + (16 * P + r) * kCB + 8 * g + 4);
-                    x[0] = x0.x; x[1] = x0.y; x[2] = x0.z; x[3] = x0.w;
-                    x[4] = x1.x; x[5] = x1.y; x[6] = x1.z; x[7] = x1.w;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned int hp = pack_bf16(x[2 * j], x[2 * j + 1]);
-                    hi[P][j] = hp;
-                    lo[P][j] = pack_bf16(x[2 * j] - __uint_as_float(hp << 16), x[2 * j + 1] - __uint_as_float(hp & 0xFFFF0000u));
-                }
-            }
-            float* dst = a.pt + (i * (lmax + 1) + l) * int64_t(QQ);
-#pragma unroll
-            for (int P1 = 0; P1 < QT; ++P1)
-#pragma unroll
-                for (int P2 = P1; P2 < QT; ++P2) {
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hi[P1]),
-                                                                  __builtin_bit_cast(bf16x8, hi[P2]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hi[P1]),
-                                                                  __builtin_bit_cast(bf16x8, lo[P2]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lo[P1]),
-                                                                  __builtin_bit_cast(bf16x8, hi[P2]), acc, 0, 0, 0);
-                    // lane holds p~[p1][p2], p1 = 16 P1 + 4 g + v, p2 = 16 P2 + r
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int at = packed(P1, P2, v);
-                        if (at >= 0) dst[at] = acc[v];
-                    }
-                }
+            spectrum_out<MT, QT>(cb, Q, r, g, a.pt + (i * (lmax + 1) + l) * int64_t(QQ));
             wave_sync();
         }
     };
@@ -1337,34 +1153,22 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
     const float* wl = a.w;
     for (int l = 0; l <= lmax; ++l, wl += lsize) {
         __syncthreads();   // the weights of l - 1 are no longer read
-        if constexpr (IMG) {
-            // l's image is in buffer l % 2 once every wave's loads are done;
-            // buffer (l + 1) % 2 held l - 1, which no wave reads any more
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-            if (l < lmax) fetch_image(l + 1);
-            const unsigned char* wb = smem_raw + (l & 1) * W.wstride;
-            W1s = reinterpret_cast<const unsigned short*>(wb + W.w1);
-            W2s = reinterpret_cast<const unsigned short*>(wb + W.w2);
-            ab = reinterpret_cast<const float*>(wb + W.ab);
-        } else {
-            __builtin_amdgcn_s_waitcnt(0);   // this wave's X of l
-            float4 wv[kWQuads];
+        __builtin_amdgcn_s_waitcnt(0);   // this wave's X of l
+        float4 wv[kWQuads];
 #pragma unroll
-            for (int u = 0; u < kWQuads; ++u)   // every load issued before any is used
-                wv[u] = *reinterpret_cast<const float4*>(wl + (wsrc[u] >= 0 ? wsrc[u] : 0));
+        for (int u = 0; u < kWQuads; ++u)   // every load issued before any is used
+            wv[u] = *reinterpret_cast<const float4*>(wl + (wsrc[u] >= 0 ? wsrc[u] : 0));
 #pragma unroll
-            for (int u = 0; u < kWQuads; ++u)
-                if (wdst[u] >= 0)
-                    wave_weight_put(smem_raw, W, wdst[u], wsrc[u] >= 0 ? wv[u] : make_float4(0.f, 0.f, 0.f, 0.f));
-            for (int e = tid + nthr * kWQuads; e < W.E; e += nthr) {   // beyond the kept offsets
-                int s0, d0;
-                wave_weight_slot(a, W, e, s0, d0);
-                wave_weight_put(smem_raw, W, d0,
-                                s0 >= 0 ? *reinterpret_cast<const float4*>(wl + s0) : make_float4(0.f, 0.f, 0.f, 0.f));
-            }
-            __syncthreads();
+        for (int u = 0; u < kWQuads; ++u)
+            if (wdst[u] >= 0)
+                wave_weight_put(smem_raw, W, wdst[u], wsrc[u] >= 0 ? wv[u] : make_float4(0.f, 0.f, 0.f, 0.f));
+        for (int e = tid + nthr * kWQuads; e < W.E; e += nthr) {   // beyond the kept offsets
+            int s0, d0;
+            wave_weight_slot(a, W, e, s0, d0);
+            wave_weight_put(smem_raw, W, d0,
+                            s0 >= 0 ? *reinterpret_cast<const float4*>(wl + s0) : make_float4(0.f, 0.f, 0.f, 0.f));
         }
+        __syncthreads();
         if (!live) continue;
         if (l < 8) degree(std::integral_constant<int, 1>{}, l);
         else degree(std::integral_constant<int, 2>{}, l);
@@ -1407,10 +1211,10 @@ hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream)
 }
 
 
-template <int QT, bool IMG, int KS, int HT>
+template <int QT, int KS, int HT>
 hipError_t launch_cmp_wave_t(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
 {
-    auto kernel = k_cmp_fwd_wave<QT, IMG, KS, HT>;
+    auto kernel = k_cmp_fwd_wave<QT, KS, HT>;
     if (W.total > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, W.total);
@@ -1420,57 +1224,45 @@ hipError_t launch_cmp_wave_t(const CompressArgs& a, const WaveLayout& W, hipStre
     return hipGetLastError();
 }
 
-template <int QT, bool IMG, int KS>
+template <int QT, int KS>
 hipError_t launch_cmp_wave_h(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
 {
-    return W.HT == 4 ? launch_cmp_wave_t<QT, IMG, KS, 4>(a, W, stream) : launch_cmp_wave_t<QT, IMG, KS, 8>(a, W, stream);
+    return W.HT == 4 ? launch_cmp_wave_t<QT, KS, 4>(a, W, stream) : launch_cmp_wave_t<QT, KS, 8>(a, W, stream);
 }
 
-template <int QT, bool IMG>
+template <int QT>
 hipError_t launch_cmp_wave_q(const CompressArgs& a, const WaveLayout& W, hipStream_t stream)
 {
-    if (IMG) {
-        hipLaunchKernelGGL(k_cmp_image, dim3(unsigned(a.lmax + 1)), dim3(256), 0, stream, a, W);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return W.KS == 1   ? launch_cmp_wave_h<QT, IMG, 1>(a, W, stream)
-           : W.KS == 2 ? launch_cmp_wave_h<QT, IMG, 2>(a, W, stream)
-           : W.KS == 3 ? launch_cmp_wave_h<QT, IMG, 3>(a, W, stream)
-                       : launch_cmp_wave_h<QT, IMG, 4>(a, W, stream);
+    return W.KS == 1   ? launch_cmp_wave_h<QT, 1>(a, W, stream)
+           : W.KS == 2 ? launch_cmp_wave_h<QT, 2>(a, W, stream)
+           : W.KS == 3 ? launch_cmp_wave_h<QT, 3>(a, W, stream)
+                       : launch_cmp_wave_h<QT, 4>(a, W, stream);
 }
 
 // the one-wave-per-centre form when the shapes fit it: K, H <= 128 and
 // multiples of 4 (weights and c read as float4), Q <= 32, 1 <= lmax <= 12
 // (a float4 of c then spans at most two lm rows), 16-byte aligned c and
 // weights, at least two centres per work-group
-bool cmp_wave_fits(const CompressArgs& a, WaveLayout& W, bool img = false)
+bool cmp_wave_fits(const CompressArgs& a, WaveLayout& W)
 {
     if (a.K > 128 || a.H > 128 || a.Q > 32 || a.lmax < 1 || a.lmax > 12) return false;
     if (a.K % 4 != 0 || a.H % 4 != 0) return false;
     if ((reinterpret_cast<uintptr_t>(a.c) & 15) != 0 || (reinterpret_cast<uintptr_t>(a.w) & 15) != 0) return false;
     for (int cpw = kWaveCentres; cpw >= 2; --cpw) {
-        W = wave_layout(a.K, a.Q, a.H, a.lmax, cpw, img);
+        W = wave_layout(a.K, a.Q, a.H, a.lmax, cpw);
         if (W.total <= 160 * 1024) return true;
     }
     return false;
-}
-
-size_t compress_image_bytes(int K, int Q, int H, int lmax)
-{
-    if (K > 128 || H > 128 || Q > 32 || lmax < 1 || lmax > 12 || K % 4 != 0 || H % 4 != 0) return 0;
-    const WaveLayout W = wave_layout(K, Q, H, lmax, 2, true);
-    return size_t(lmax + 1) * W.wstride;
 }
 
 hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t stream)
 {
     if (a.n == 0) return hipSuccess;
     WaveLayout W;
-    if (a.img && (reinterpret_cast<uintptr_t>(a.img) & 15) == 0 && cmp_wave_fits(a, W, true))
-        return a.Q <= 16 ? launch_cmp_wave_q<1, true>(a, W, stream) : launch_cmp_wave_q<2, true>(a, W, stream);
-    if (cmp_wave_fits(a, W))
-        return a.Q <= 16 ? launch_cmp_wave_q<1, false>(a, W, stream) : launch_cmp_wave_q<2, false>(a, W, stream);
+    if (cmp_wave_fits(a, W)) {
+        if (a.img) return launch_compress_infer(a, stream);
+        return a.Q <= 16 ? launch_cmp_wave_q<1>(a, W, stream) : launch_cmp_wave_q<2>(a, W, stream);
+    }
     if (a.K > 32 * kKS1 || a.H > 16 * 4 * kMT || a.Q > 64) return hipErrorNotSupported;
     const size_t lds = compress_bf16_lds(a);
     if (lds > 160 * 1024) return hipErrorNotSupported;

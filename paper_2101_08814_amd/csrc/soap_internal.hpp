@@ -198,7 +198,7 @@ struct CompressArgs {
     float* gpart;              // backward: per-slice partial gradients [slices][n_params]
     int slices;
     int32_t* status;
-    void* img;                 // bfloat16 forward: LDS image of every l's weights (device workspace) or NULL
+    void* img;                 // bfloat16 forward: room for every l's weights laid out (device workspace) or NULL
 };
 
 // bytes of the weight image of the bfloat16 forward (0 when its shapes do
@@ -211,6 +211,8 @@ size_t compress_bwd_lds(const CompressArgs& a);
 hipError_t launch_train_forward(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_train_backward(const CompressArgs& a, float* grad, hipStream_t stream);
 hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream);
+// the bfloat16 forward with a.img (compress_infer.hip)
+hipError_t launch_compress_infer(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t stream);
 hipError_t launch_compress_backward(const CompressArgs& a, float* grad, hipStream_t stream);
 hipError_t launch_channel_cov(const CompressArgs& a, float* part, int slices, hipStream_t stream);
