@@ -2,8 +2,8 @@
 // a workspace: c of a centre is read from HBM once, as one contiguous run.
 //
 // One wave per centre and per work-group; no work-group barriers.
-//   c        the centre's K x L2 floats, loaded 64 consecutive elements at a
-//            time, rounded to bfloat16 and put into the wave's LDS as rows
+//   c        the centre's K x L2 floats, loaded 64 consecutive columns of a
+//            channel at a time, rounded to bfloat16 and put into the wave's LDS as rows
 //            [lm][k], so that a layer-1 operand is one 16-byte read.
 //   per l    the columns of every product are the m of the centre (one
 //            16-wide tile, two when 2l + 1 > 16):
@@ -130,48 +130,44 @@ __global__ void __launch_bounds__(64, 2) k_cmp_infer(CompressArgs a, InferLayout
         for (int f = 0; f < N1; ++f) w1[f] = src[f * 64 + lane];
     };
 
-    // c -> X.  Element pair f = 64 it + lane is (kp, lm) = (f / L2, f % L2):
-    // channels 2 kp and 2 kp + 1 of column lm; loads past the centre's array
-    // (channels past K) return zero.
+    // c -> X.  Element f = 64 it + lane is (kq, lm) = (f / L2, f % L2): the
+    // four channels 4 kq + j of column lm (K is a multiple of 4), one 8-byte
+    // store; loads past the centre's array (channels past K) return zero.
     {
         const uint64_t c0 = reinterpret_cast<uint64_t>(a.c + i * int64_t(K) * L2);
         const uint64_t base = (uint64_t(unsigned(uniform(int(c0 >> 32)))) << 32) | unsigned(uniform(int(c0)));
         const int next = uniform(L2 * 4);   // bytes from a channel to the next one
         const __amdgpu_buffer_rsrc_t src =
             __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), 0, uniform(K * L2 * 4), 0x00020000);
-        constexpr int kBatch = 16;   // pairs in flight per lane; the next batch is loaded before this one is stored
-        const int n = (16 * KS) * L2;
-        const int da = L.da, dm = L.dm;
-        const int kp = int((float(lane) + 0.5f) / float(L2));
-        int lm = lane - kp * L2;
-        int at = lm * XS + kp;            // where the next pair goes
-        int from = (2 * kp * L2 + lm) * 4;
-        int lm_from = lm;
-        unsigned v[2][kBatch][2];
+        constexpr int kBatch = 8;   // elements in flight per lane; the next batch is loaded before this one is stored
+        const int n = (8 * KS) * L2;
+        const int dm = L.dm, step_from = (4 * L.da * L2 + dm) * 4, step_at = dm * XS + 2 * L.da;
+        const int wrap_from = 3 * next, wrap_at = 2 - L2 * XS;
+        const int kq = int((float(lane) + 0.5f) / float(L2));
+        int lm = lane - kq * L2, from = (4 * kq * L2 + lm) * 4, to = lm * XS + 2 * kq;
+        unsigned v[2][kBatch][4];
+        int at[2][kBatch];
         auto load = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                v[b][u][0] = __builtin_amdgcn_raw_buffer_load_b32(src, from, 0, 0);
-                v[b][u][1] = __builtin_amdgcn_raw_buffer_load_b32(src, from, next, 0);
-                lm_from += dm;
-                from += (2 * da * L2 + dm) * 4;
-                if (lm_from >= L2) {
-                    lm_from -= L2;
-                    from += L2 * 4;
-                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[b][u][j] = __builtin_amdgcn_raw_buffer_load_b32(src, from, j * next, 0);
+                at[b][u] = to;
+                lm += dm;
+                const bool wrap = lm >= L2;
+                lm -= wrap ? L2 : 0;
+                from += step_from + (wrap ? wrap_from : 0);
+                to += step_at + (wrap ? wrap_at : 0);
             }
         };
         auto store = [&](int b, int f0) __attribute__((always_inline)) {
+            const bool whole = f0 + 64 * kBatch <= n;
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                if (f0 + 64 * u + lane < n) X[at] = pack_bf16(__uint_as_float(v[b][u][0]), __uint_as_float(v[b][u][1]));
-                lm += dm;
-                at += dm * XS + da;
-                if (lm >= L2) {
-                    lm -= L2;
-                    at += 1 - L2 * XS;
-                }
-            }
+            for (int u = 0; u < kBatch; ++u)
+                if (whole || f0 + 64 * u + lane < n)
+                    *reinterpret_cast<uint2*>(X + at[b][u]) =
+                        make_uint2(pack_bf16(__uint_as_float(v[b][u][0]), __uint_as_float(v[b][u][1])),
+                                   pack_bf16(__uint_as_float(v[b][u][2]), __uint_as_float(v[b][u][3])));
         };
         load(0);
         for (int f0 = 0; f0 < n; f0 += 2 * 64 * kBatch) {
