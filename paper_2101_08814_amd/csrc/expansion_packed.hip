@@ -4,12 +4,22 @@
 //
 // A wave takes a few consecutive centres and walks their pairs, which are
 // stored contiguously and grouped by centre and then by neighbour species,
-// in chunks of 32: a chunk may hold the end of one centre and the start of
-// the next, so the lanes stay busy when centres have few pairs.  Both
-// halves of the wave stage the same 32 pairs: each lane forms its pair's
-// geometry and harmonics Y_lm (both halves write the same values to the
-// wave's LDS rows) and half of its radial values R_nl = f I~_nl, four n at
-// a time with one 16-byte LDS store.  Each lane then owns up to
+// in chunks of 16: a chunk may hold the end of one centre and the start of
+// the next, so the lanes stay busy when centres have few pairs.  All four
+// quarters of the wave form the same 16 pairs' geometry and harmonics Y_lm
+// (and write the same values to the wave's LDS rows); the radial values
+// R_nl = f I~_nl are formed by four lanes per pair, neighbouring lanes on
+// neighbouring cubics of the pair's interval, so that a load takes 64-byte
+// runs of 16 pairs and not 16 bytes of each of 64 lines.  Chunks of 16 halve
+// the LDS of a wave (12.6 KB at nmax 12, lmax 8), which lets eight waves share
+// a CU where chunks of 32 with two lanes per pair let six; forming the
+// harmonics four times over costs less than the waves gain: 131,072 centres
+// at nmax 12, lmax 8 (4.1 GB written) 1.72 -> 1.44 ms, a 4096-atom liquid at
+// nmax 10, lmax 8 68 -> 61 us, 28,924 centres at nmax 8, lmax 6 116 us either
+// way.  Either change alone is slower or gives a third of that (cooperative
+// loads in chunks of 32: 1.75 ms, chunks of 16 with a lane per quad: 1.57).
+// Sums on v_mfma_f32_4x4x1 (four n and an m per lane): 1.46 to 1.56 ms.
+// Each lane then owns up to
 // pack_slots items (four n, one lm) of c and sums R_{n..n+3,l} Y_lm over
 // the pairs of the current (centre, species) segment in registers; when
 // the segment ends the sums go straight to HBM (consecutive lanes on
@@ -24,9 +34,12 @@ namespace {
 
 using namespace dev;
 
-constexpr int kPackCh = 32;      // pairs per chunk, two lanes per pair
+constexpr int kPackCh = 16;      // pairs per chunk, four lanes per pair
 constexpr int kPackMaxCpw = 4;   // centres per wave
 constexpr int kPackMaxN = 16;    // nmax covered by the register items
+
+// quads of an LDS row of radial values
+__host__ __device__ constexpr int pack_quads(int lm1, int gmax) { return (lm1 * gmax) | 1; }
 
 // items per lane with at most GMAX groups of four n (nmax <= 4 GMAX)
 template <int LMAX, int GMAX>
@@ -48,10 +61,10 @@ template <typename T, int LMAX, int GMAX>
 __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion_packed(FeatureArgs a, PackLayout W)
 {
     constexpr int LM1 = LMAX + 1, L2 = LM1 * LM1, NS = pack_slots<LMAX, GMAX>();
-    constexpr int kNB = GMAX <= 2 ? 3 : 2;   // radial quads in flight
-    // LDS rows of a pair: radial values [l][4 GMAX] and a spare quad, and
-    // the harmonics (odd stride)
-    constexpr int NP = 4 * GMAX, NLS = LM1 * NP + 4, L2S = L2 | 1;
+    // LDS rows of a pair: radial values [l][4 GMAX] (an odd number of quads,
+    // so that the rows of 16 pairs start on distinct banks), and the
+    // harmonics (odd stride)
+    constexpr int NP = 4 * GMAX, NLS = 4 * pack_quads(LM1, GMAX), L2S = L2 | 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* Rs = reinterpret_cast<T*>(smem_raw);   // [pair][NLS] radial values
     T* Ys = Rs + kPackCh * NLS;                // [pair][L2S] harmonics
@@ -61,9 +74,8 @@ __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion
         return;
     }
     const int nmax = a.nmax, S = a.S, G = W.G;
-    const int nL2 = nmax * L2, NI = G * L2, nq = LM1 * G;
+    const int nL2 = nmax * L2, NI = G * L2;
     const int nl = LM1 * nmax;
-    const int pad = 4 * G - nmax, gmul = (65536 + G - 1) / G;   // l of quad u: (u * gmul) >> 16
     const int64_t c0 = int64_t(blockIdx.x) * W.cpw;
     const int ncw = int(a.n_atoms - c0 < W.cpw ? a.n_atoms - c0 : W.cpw);
     int64_t bnd[kPackMaxCpw + 1];   // pair range of each of the wave's centres
@@ -77,6 +89,7 @@ __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion
     // items v = lane + 64 u (u < NS, v < NI): n = 4 ng .. 4 ng + 3 of one lm;
     // lanes past NI in the last slot read row 0 and write nothing
     int yoff[NS], roff[NS];
+    unsigned ooff[NS];   // bytes of the item in a block of c
     V4<T> acc[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
@@ -85,12 +98,15 @@ __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion
         const bool in = v < NI;
         yoff[u] = in ? lm : 0;
         roff[u] = in ? l_of(lm) * NP + 4 * ng : 0;
+        ooff[u] = unsigned(4 * ng * L2 + lm) * unsigned(sizeof(T));
         acc[u] = V4<T>{T(0), T(0), T(0), T(0)};
     }
     // the central atom's terms in LDS, so that writing a block waits on no
     // global load
     T* Cs = Ys + kPackCh * L2S;
     if (lane < kPackMaxN) Cs[lane] = lane < nmax ? centre_term[lane] : T(0);
+    // {t, f, interval} of the chunk's pairs
+    T* Gs = Cs + kPackMaxN;
     // species of the wave's centres, 16 bits each (0xFFFF: no central term)
     uint64_t cspc = ~uint64_t(0);
 #pragma unroll
@@ -143,64 +159,81 @@ __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion
     // Pair q0 + p staged by both halves; returns its key (centre of the
     // wave) S + (neighbour species), -1 past the chunk.
     auto stage = [&](int64_t q0, int nc, const PairIn& in, int spq) __attribute__((always_inline)) -> int {
-        const int p = lane & (kPackCh - 1), h = lane >> 5;
+        const int p = lane & (kPackCh - 1);
         int key = -1;
-        if (p < nc) {
-            const int64_t q = q0 + p;
-            const PairGeom<T> g = pair_geometry<T>(a, in.x, in.y, in.z);
-            int cl = 0;
+        T ux = T(0), uy = T(0), uz = T(1);
+        {
+            T t = T(0), f = T(0);
+            int k = 0;
+            if (p < nc) {
+                const int64_t q = q0 + p;
+                const PairGeom<T> g = pair_geometry<T>(a, in.x, in.y, in.z);
+                int cl = 0;
 #pragma unroll
-            for (int k = 1; k < kPackMaxCpw; ++k) cl += q >= bnd[k] ? 1 : 0;
-            key = cl * S + spq;
-            const V4<T>* cf = coef + int64_t(g.k) * nl;
-            T* rrow = Rs + p * NLS;
-            const T tt = g.t, f = g.f;
-            // radial quads u = h + 2 i: four n of one l, coefficient
-            // j = l nmax + 4 (u - l G) = 4 u - l pad, LDS l NP + 4 (u - l G)
-            // = 4 u + 4 l (GMAX - G).
-            // The last quad of a degree may read up to three values past it
-            // (the next interval's, or the table's zero tail), which land in
-            // the row's padding.  Every lane takes QH quads: those past nq
-            // read the last quad's coefficients and write the row's spare
-            // quad, so that each load is used on every path.
-            constexpr int QH = (LM1 * GMAX + 1) / 2;
-            auto coefs = [&](int u, V4<T>* A) __attribute__((always_inline)) {
-                u = u < nq ? u : nq - 1;
-                const int j = 4 * u - ((u * gmul) >> 16) * pad;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) A[k] = cf[j + k];
-            };
-            auto put = [&](int u, const V4<T>* A) __attribute__((always_inline)) {
-                const int o = u < nq ? 4 * u + 4 * ((u * gmul) >> 16) * (GMAX - G) : LM1 * NP;
-                V4<T> r;
-                r.x = f * (A[0].x + tt * (A[0].y + tt * (A[0].z + tt * A[0].w)));
-                r.y = f * (A[1].x + tt * (A[1].y + tt * (A[1].z + tt * A[1].w)));
-                r.z = f * (A[2].x + tt * (A[2].y + tt * (A[2].z + tt * A[2].w)));
-                r.w = f * (A[3].x + tt * (A[3].y + tt * (A[3].z + tt * A[3].w)));
-                *reinterpret_cast<V4<T>*>(rrow + o) = r;
-            };
-            // the first three quads in flight during the harmonics, then each
-            // buffer refilled with the quad three ahead
-            constexpr int NB = QH < kNB ? QH : kNB;
-            V4<T> Bf[NB][4];
-            static_for<0, NB>([&](auto I) __attribute__((always_inline)) {
-                constexpr int i = decltype(I)::value;
-                coefs(h + 2 * i, Bf[i]);
-            });
-            T* yrow = Ys + p * L2S;
-            YlmStream<T, LMAX> ys(g.ux, g.uy, g.uz);
-            static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
-                constexpr int L = decltype(Lc)::value;
-                ys.template degree<L, false>([&](int mi, T Y, T, T, T) __attribute__((always_inline)) {
-                    yrow[L * L + mi] = Y;
-                });
-            });
-            static_for<0, QH>([&](auto I) __attribute__((always_inline)) {
-                constexpr int i = decltype(I)::value;
-                put(h + 2 * i, Bf[i % NB]);
-                if constexpr (i + NB < QH) coefs(h + 2 * (i + NB), Bf[i % NB]);
-            });
+                for (int c = 1; c < kPackMaxCpw; ++c) cl += q >= bnd[c] ? 1 : 0;
+                key = cl * S + spq;
+                ux = g.ux; uy = g.uy; uz = g.uz;
+                t = g.t; f = g.f; k = g.k;
+            }
+            if (lane < kPackCh) *reinterpret_cast<V4<T>*>(Gs + 4 * p) = V4<T>{t, f, T(k), T(0)};
         }
+        wave_sync();
+        // radial values: lane = 4 pl + part takes the cubics j = part + 4 i of
+        // pair pl (past the interval: the next one's, or the table's zero
+        // tail, not stored), kNB at a time, the first in flight during the
+        // harmonics and each next batch during the last
+        constexpr int NQ = LM1 * GMAX, kNB = 6, NBAT = (NQ + kNB - 1) / kNB;
+        const int part = lane & 3, pl = lane >> 2, ni = (nl + 3) >> 2;
+        const V4<T> gq = *reinterpret_cast<const V4<T>*>(Gs + 4 * pl);
+        const T tt = gq.x, ff = gq.y;
+        const V4<T>* cf = coef + int64_t(int(gq.z)) * nl + part;
+        V4<T> A[2][kNB];
+        auto fetch = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kNB; ++i) A[b & 1][i] = cf[4 * (b * kNB + i)];
+        };
+        // LDS position of the lane's next value: l NP + n for j = l nmax + n
+        int rn = part, ro = part;
+        auto settle = [&]() __attribute__((always_inline)) {
+            const bool w = rn >= nmax;
+            rn -= w ? nmax : 0;
+            ro += w ? NP - nmax : 0;
+            if (nmax < 4)   // up to four degrees per step
+                while (rn >= nmax) {
+                    rn -= nmax;
+                    ro += NP - nmax;
+                }
+        };
+        settle();
+        T* rrow = Rs + pl * NLS;
+        auto use = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kNB; ++i) {
+                const V4<T> c = A[b & 1][i];
+                if (ro < LM1 * NP) rrow[ro] = ff * (c.x + tt * (c.y + tt * (c.z + tt * c.w)));
+                rn += 4;
+                ro += 4;
+                settle();
+            }
+        };
+        fetch(0);
+        T* yrow = Ys + p * L2S;
+        YlmStream<T, LMAX> ys(ux, uy, uz);
+        static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
+            constexpr int L = decltype(Lc)::value;
+            ys.template degree<L, false>([&](int mi, T Y, T, T, T) __attribute__((always_inline)) {
+                yrow[L * L + mi] = Y;
+            });
+        });
+        static_for<0, NBAT>([&](auto Bc) __attribute__((always_inline)) {
+            constexpr int b = decltype(Bc)::value;
+            if (b * kNB < ni) {
+                if constexpr (b + 1 < NBAT) {
+                    if ((b + 1) * kNB < ni) fetch(b + 1);
+                }
+                use(b);
+            }
+        });
         wave_sync();
         return key;
     };
@@ -259,7 +292,7 @@ __global__ void __launch_bounds__(64, (pack_waves<T, LMAX, GMAX>())) k_expansion
                     x4[k] += cen ? ck : T(0);
                 }
             }
-            T* o = out + 4 * ng * L2 + lm;
+            T* o = reinterpret_cast<T*>(reinterpret_cast<char*>(out) + ooff[u]);
             if (nn == 4) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) o[k * L2] = x4[k];
@@ -374,14 +407,16 @@ PackLayout pack_layout(int nmax, int lmax, int64_t n_atoms, int64_t pair_capacit
     const int lm1 = lmax + 1;
     W.G = (nmax + 3) / 4;
     W.gmax = W.G < 2 ? 2 : W.G;   // the kernel's radial rows hold 4 gmax n per l
-    const int nls = lm1 * 4 * W.gmax + 4, l2s = (lm1 * lm1) | 1;   // a spare quad per row
-    W.total = kPackCh * (nls + l2s) + kPackMaxN;
-    // enough waves to fill the chip before centres are packed; centres with
-    // a chunk of pairs or more each gain little from sharing a wave
-    // (4096-atom liquid, 45 pairs per centre: 86 us at one centre per wave,
-    // 96 at two or four)
-    const bool long_envs = pair_capacity >= int64_t(kPackCh) * n_atoms;
-    W.cpw = long_envs ? 1 : n_atoms >= 8192 ? 4 : n_atoms >= 2048 ? 2 : 1;
+    const int nls = 4 * pack_quads(lm1, W.gmax), l2s = (lm1 * lm1) | 1;
+    W.total = kPackCh * (nls + l2s) + kPackMaxN + 4 * kPackCh;
+    // enough waves to fill the chip before centres are packed; below 8192
+    // centres those whose environments fill chunks gain little from sharing a
+    // wave (4096-atom liquid, 45 pairs per centre: 86 us at one centre per
+    // wave, 96 at two or four), above it the wave's set-up is worth sharing
+    // whatever their size (131,072 centres of 31 pairs: 1.72 ms at one, 1.58
+    // at four, with chunks of 32)
+    const bool long_envs = pair_capacity >= 2 * int64_t(kPackCh) * n_atoms;
+    W.cpw = n_atoms >= 8192 ? 4 : long_envs ? 1 : n_atoms >= 2048 ? 2 : 1;
     return W;
 }
 
