@@ -878,6 +878,7 @@ constexpr int kBruteBatch = 4;   // rounds of 64 candidates whose positions are 
 
 struct BruteCentre {
     bool ok;          // the whole input is valid
+    bool periodic;    // along any axis
     int64_t lo, hi;   // atoms of the centre's structure
     double ri[3];
     double e[3];      // rcut / width per periodic axis (with a margin), 0 otherwise
@@ -894,15 +895,24 @@ __device__ BruteCentre brute_centre(const NeighborArgs& a, int64_t i, StructGeom
     const int ns = a.n_structures;
     BruteCentre c;
     int s;
+    for (int k = 0; k < 3; ++k) c.ri[k] = a.positions[3 * i + k];   // on their way during the search
     if constexpr (GEOM) {
         c.ok = *a.ok != 0;
-        int lo = 0, hi = ns - 1;   // first structure ending after i (the offsets are contiguous and cached)
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (a.atom_offsets[mid + 1] > i) hi = mid; else lo = mid + 1;
+        // first structure ending after i, 64 probes at a time (one lane's
+        // binary search waited for nine loads in turn at 512 structures)
+        int lo = 0, hi = ns;
+        while (hi - lo > 1) {
+            const int step = (hi - lo + 63) >> 6, p = lo + (lane + 1) * step - 1;
+            const int ended = __popcll(__ballot(p < hi && a.atom_offsets[p < hi ? p + 1 : ns] <= i));
+            lo += ended * step;
+            if (lo > ns - 1) lo = ns - 1;
+            hi = hi < lo + step ? hi : lo + step;
+            if (step == 1) break;
         }
         s = lo;
-        if (lane == 0) gs = a.geom[s];
+        static_assert(sizeof(StructGeom) % 8 == 0 && sizeof(StructGeom) <= 64 * 8, "one word per lane");
+        if (lane < int(sizeof(StructGeom) / 8))
+            reinterpret_cast<int64_t*>(&gs)[lane] = reinterpret_cast<const int64_t*>(a.geom + s)[lane];
     } else {
         StructGeom g;
         bool bad = false;
@@ -920,23 +930,30 @@ __device__ BruteCentre brute_centre(const NeighborArgs& a, int64_t i, StructGeom
     c.lo = gs.atom_lo;
     c.hi = gs.atom_hi;
     if (s >= ns || !(c.lo <= i && i < c.hi)) c.ok = false;
-    for (int k = 0; k < 3; ++k) {
-        c.ri[k] = a.positions[3 * i + k];
+    c.periodic = __builtin_amdgcn_readfirstlane(gs.pbc[0] | gs.pbc[1] | gs.pbc[2]) != 0;
+    for (int k = 0; k < 3; ++k) c.e[k] = 0.0;
+    if (c.periodic) {
+        const int k = lane < 2 ? lane : 2;   // lane k forms axis k's
         const double bk = sqrt(gs.Hinv[0 * 3 + k] * gs.Hinv[0 * 3 + k] + gs.Hinv[1 * 3 + k] * gs.Hinv[1 * 3 + k] +
                                gs.Hinv[2 * 3 + k] * gs.Hinv[2 * 3 + k]);
-        c.e[k] = gs.pbc[k] ? a.rcut * bk * (1.0 + 1e-9) + 1e-12 : 0.0;
+        const double ek = gs.pbc[k] ? a.rcut * bk * (1.0 + 1e-9) + 1e-12 : 0.0;
+        for (int x = 0; x < 3; ++x) c.e[x] = __shfl(ek, x, 64);
     }
     return c;
 }
 
 // every candidate j of centre i, kBruteBatch rounds of 64 at a time:
-// emit(hit, j, s0, s1, s2, vx, vy, vz) by every lane for every image step
+// emit(hit, j, s0, s1, s2, vx, vy, vz) by every lane for every image step.
+// Returns whether no candidate had more than one image (cells at least 2 rcut
+// wide, molecules), in which case no step divides by image counts and the
+// hits come out in ascending j.
 template <class F>
-__device__ void brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre& c, const StructGeom& g, F&& emit)
+__device__ bool brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre& c, const StructGeom& g, F&& emit)
 {
     const int lane = threadIdx.x & 63;
     const double rc2 = a.rcut * a.rcut;
     const int64_t lo = c.ok ? c.lo : 0, hi = c.ok ? c.hi : 0;
+    bool single = true;
     for (int64_t j0 = lo; j0 < hi; j0 += 64 * kBruteBatch) {
         double rj[kBruteBatch][3];
 #pragma unroll
@@ -948,8 +965,27 @@ __device__ void brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre&
 #pragma unroll
         for (int r = 0; r < kBruteBatch; ++r) {
             const int64_t j = j0 + 64 * r + lane;
-            if (__ballot(j < hi) == 0) break;
+            if (j0 + 64 * r >= hi) break;
             const double d0 = rj[r][0] - c.ri[0], d1 = rj[r][1] - c.ri[1], d2 = rj[r][2] - c.ri[2];
+            auto test = [&](bool in, int s0, int s1, int s2, double vx, double vy, double vz) __attribute__((always_inline)) {
+                bool hit = false;
+                if (in && !(j == i && s0 == 0 && s1 == 0 && s2 == 0)) {
+                    const double r2 = vx * vx + vy * vy + vz * vz;
+                    if (r2 < rc2) {
+                        if (r2 == 0.0) put_status(a.status, SOAP_EGEOMETRY);
+                        else hit = true;
+                    }
+                }
+                emit(hit, int(j), s0, s1, s2, vx, vy, vz);
+            };
+            auto image = [&](bool in, int s0, int s1, int s2) __attribute__((always_inline)) {
+                test(in, s0, s1, s2, d0 + s0 * g.H[0] + s1 * g.H[3] + s2 * g.H[6],
+                     d1 + s0 * g.H[1] + s1 * g.H[4] + s2 * g.H[7], d2 + s0 * g.H[2] + s1 * g.H[5] + s2 * g.H[8]);
+            };
+            if (!c.periodic) {
+                test(j < hi, 0, 0, 0, d0, d1, d2);
+                continue;
+            }
             // box of shifts: s_k in [ceil(-f_k - e_k), floor(-f_k + e_k)]
             int smin[3], cnt[3];
             int n_img = j < hi ? 1 : 0;
@@ -964,31 +1000,25 @@ __device__ void brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre&
                 }
                 n_img *= cnt[k];
             }
+            if (__ballot(n_img > 1) == 0) {
+                image(n_img == 1, smin[0], smin[1], smin[2]);
+                continue;
+            }
+            single = false;
             int n_max = n_img;
             for (int off = 32; off > 0; off >>= 1) n_max = max(n_max, __shfl_xor(n_max, off, 64));
             for (int t = 0; t < n_max; ++t) {
-                bool hit = false;
                 int s0 = 0, s1 = 0, s2 = 0;
-                double vx = 0.0, vy = 0.0, vz = 0.0;
                 if (t < n_img) {
                     s2 = smin[2] + t % cnt[2];
                     s1 = smin[1] + (t / cnt[2]) % cnt[1];
                     s0 = smin[0] + t / (cnt[2] * cnt[1]);
-                    if (!(j == i && s0 == 0 && s1 == 0 && s2 == 0)) {
-                        vx = d0 + s0 * g.H[0] + s1 * g.H[3] + s2 * g.H[6];
-                        vy = d1 + s0 * g.H[1] + s1 * g.H[4] + s2 * g.H[7];
-                        vz = d2 + s0 * g.H[2] + s1 * g.H[5] + s2 * g.H[8];
-                        const double r2 = vx * vx + vy * vy + vz * vz;
-                        if (r2 < rc2) {
-                            if (r2 == 0.0) put_status(a.status, SOAP_EGEOMETRY);
-                            else hit = true;
-                        }
-                    }
                 }
-                emit(hit, int(j), s0, s1, s2, vx, vy, vz);
+                image(t < n_img, s0, s1, s2);
             }
         }
     }
+    return single;
 }
 
 template <bool GEOM>
@@ -1059,7 +1089,7 @@ __global__ void __launch_bounds__(64) k_fill_bf(NeighborArgs a)
     const BruteCentre c = brute_centre<GEOM>(a, i, gs);
     const bool in_lds = n <= kBruteSortCap;
     int count = 0;
-    brute_visit(a, i, c, gs, [&](bool hit, int j, int s0, int s1, int s2, double vx, double vy, double vz) {
+    const bool single = brute_visit(a, i, c, gs, [&](bool hit, int j, int s0, int s1, int s2, double vx, double vy, double vz) {
         const uint64_t mask = __ballot(hit);
         const int idx = count + __popcll(mask & ((uint64_t(1) << lane) - 1));
         if (hit && idx < n) {
@@ -1077,23 +1107,57 @@ __global__ void __launch_bounds__(64) k_fill_bf(NeighborArgs a)
         count += __popcll(mask);
     });
     __syncthreads();
+    VT* vec = static_cast<VT*>(a.pair_vec);
+    auto put = [&](int p, int rank) __attribute__((always_inline)) {
+        const int64_t q = o0 + rank;
+        a.pair_j[q] = kj[p];
+        a.pair_shift[3 * q] = ks[3 * p];
+        a.pair_shift[3 * q + 1] = ks[3 * p + 1];
+        a.pair_shift[3 * q + 2] = ks[3 * p + 2];
+        vec[3 * q] = kv[3 * p];
+        vec[3 * q + 1] = kv[3 * p + 1];
+        vec[3 * q + 2] = kv[3 * p + 2];
+    };
+    // in ascending j already, and every species valid (the count reports the
+    // others): a stable count by species (the records of lane and lane + 64),
+    // one ballot per species
+    static_assert(kBruteSortCap == 128, "two records per lane");
+    int sp[2] = {-1, -1};
+    bool counts = in_lds && single;
+    if (counts) {
+        bool bad = false;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (lane + 64 * h < n) {
+                sp[h] = a.species[kj[lane + 64 * h]];
+                bad = bad || sp[h] < 0 || sp[h] >= a.n_species;
+            }
+        counts = __ballot(bad) == 0;
+    }
+    if (counts) {
+        int rank[2] = {0, 0};
+        const uint64_t below = (uint64_t(1) << lane) - 1;
+        int base = 0;
+        for (int v = 0; v < a.n_species && base < n; ++v) {
+            const uint64_t m0 = __ballot(sp[0] == v), m1 = n > 64 ? __ballot(sp[1] == v) : 0;
+            const int c0 = __popcll(m0);
+            if (sp[0] == v) rank[0] = base + __popcll(m0 & below);
+            if (sp[1] == v) rank[1] = base + c0 + __popcll(m1 & below);
+            base += c0 + __popcll(m1);
+        }
+        if (lane < n) put(lane, rank[0]);
+        if (lane + 64 < n) put(lane + 64, rank[1]);
+        return;
+    }
     if (in_lds) {
         for (int p = lane; p < n; p += 64) make_key(a.species[kj[p]], kj[p], ks[3 * p], ks[3 * p + 1], ks[3 * p + 2],
                                                     khi[p], klo[p]);
         __syncthreads();
-        VT* vec = static_cast<VT*>(a.pair_vec);
         for (int p = lane; p < n; p += 64) {
             const int64_t h = khi[p], l = klo[p];
             int rank = 0;
             for (int q = 0; q < n; ++q) rank += key_less(khi[q], klo[q], h, l) ? 1 : 0;
-            const int64_t q = o0 + rank;
-            a.pair_j[q] = kj[p];
-            a.pair_shift[3 * q] = ks[3 * p];
-            a.pair_shift[3 * q + 1] = ks[3 * p + 1];
-            a.pair_shift[3 * q + 2] = ks[3 * p + 2];
-            vec[3 * q] = kv[3 * p];
-            vec[3 * q + 1] = kv[3 * p + 1];
-            vec[3 * q + 2] = kv[3 * p + 2];
+            put(p, rank);
         }
         return;
     }
