@@ -879,6 +879,8 @@ constexpr int kBruteBatch = 4;   // rounds of 64 candidates whose positions are 
 struct BruteCentre {
     bool ok;          // the whole input is valid
     bool periodic;    // along any axis
+    bool nearest;     // every periodic width over 2 rcut: only the nearest image of an atom can be within rcut
+    bool diagonal;    // the lattice vectors lie along x, y and z
     int64_t lo, hi;   // atoms of the centre's structure
     double ri[3];
     double e[3];      // rcut / width per periodic axis (with a margin), 0 otherwise
@@ -932,12 +934,15 @@ __device__ BruteCentre brute_centre(const NeighborArgs& a, int64_t i, StructGeom
     if (s >= ns || !(c.lo <= i && i < c.hi)) c.ok = false;
     c.periodic = __builtin_amdgcn_readfirstlane(gs.pbc[0] | gs.pbc[1] | gs.pbc[2]) != 0;
     for (int k = 0; k < 3; ++k) c.e[k] = 0.0;
+    c.nearest = c.diagonal = false;
     if (c.periodic) {
         const int k = lane < 2 ? lane : 2;   // lane k forms axis k's
         const double bk = sqrt(gs.Hinv[0 * 3 + k] * gs.Hinv[0 * 3 + k] + gs.Hinv[1 * 3 + k] * gs.Hinv[1 * 3 + k] +
                                gs.Hinv[2 * 3 + k] * gs.Hinv[2 * 3 + k]);
         const double ek = gs.pbc[k] ? a.rcut * bk * (1.0 + 1e-9) + 1e-12 : 0.0;
         for (int x = 0; x < 3; ++x) c.e[x] = __shfl(ek, x, 64);
+        c.nearest = __ballot(!(ek < 0.5)) == 0;
+        c.diagonal = __ballot(lane < 9 && lane % 4 != 0 && gs.H[lane < 9 ? lane : 0] != 0.0) == 0;
     }
     return c;
 }
@@ -984,6 +989,27 @@ __device__ bool brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre&
             };
             if (!c.periodic) {
                 test(j < hi, 0, 0, 0, d0, d1, d2);
+                continue;
+            }
+            if (c.nearest) {
+                // |f_k + s_k| < 1/2 allows s_k = rint(-f_k) alone, and the
+                // distance decides; off-diagonal terms of a diagonal cell are
+                // products with zero
+                double f0 = d0 * g.Hinv[0], f1 = d1 * g.Hinv[4], f2 = d2 * g.Hinv[8];
+                if (!c.diagonal) {
+                    f0 = d0 * g.Hinv[0] + d1 * g.Hinv[3] + d2 * g.Hinv[6];
+                    f1 = d0 * g.Hinv[1] + d1 * g.Hinv[4] + d2 * g.Hinv[7];
+                    f2 = d0 * g.Hinv[2] + d1 * g.Hinv[5] + d2 * g.Hinv[8];
+                }
+                const double s0 = g.pbc[0] ? rint(-f0) : 0.0, s1 = g.pbc[1] ? rint(-f1) : 0.0,
+                             s2 = g.pbc[2] ? rint(-f2) : 0.0;
+                double vx = d0 + s0 * g.H[0], vy = d1 + s1 * g.H[4], vz = d2 + s2 * g.H[8];
+                if (!c.diagonal) {
+                    vx = d0 + s0 * g.H[0] + s1 * g.H[3] + s2 * g.H[6];
+                    vy = d1 + s0 * g.H[1] + s1 * g.H[4] + s2 * g.H[7];
+                    vz = d2 + s0 * g.H[2] + s1 * g.H[5] + s2 * g.H[8];
+                }
+                test(j < hi, int(s0), int(s1), int(s2), vx, vy, vz);
                 continue;
             }
             // box of shifts: s_k in [ceil(-f_k - e_k), floor(-f_k + e_k)]
