@@ -947,6 +947,19 @@ __device__ BruteCentre brute_centre(const NeighborArgs& a, int64_t i, StructGeom
     return c;
 }
 
+// brute_centre for the first centre of a wave and where a structure ends;
+// otherwise the wave's last structure serves
+template <bool GEOM>
+__device__ __forceinline__ void next_centre(const NeighborArgs& a, int64_t i, bool fresh, BruteCentre& c, StructGeom& gs)
+{
+    if (fresh || !(c.lo <= i && i < c.hi)) {
+        wave_fence();   // the geometry is not read any more
+        c = brute_centre<GEOM>(a, i, gs);
+    } else {
+        for (int k = 0; k < 3; ++k) c.ri[k] = a.positions[3 * i + k];
+    }
+}
+
 // every candidate j of centre i, kBruteBatch rounds of 64 at a time:
 // emit(hit, j, s0, s1, s2, vx, vy, vz) by every lane for every image step.
 // Returns whether no candidate had more than one image (cells at least 2 rcut
@@ -1047,21 +1060,32 @@ __device__ bool brute_visit(const NeighborArgs& a, int64_t i, const BruteCentre&
     return single;
 }
 
-template <bool GEOM>
+// CPW consecutive centres per wave: four from kBruteShare centres on, where
+// the chip is full either way and a wave's structure search and geometry are
+// worth sharing (131,072 centres: 150 us at one, 123 at four; 28,924: 24 and
+// 25; the fill, with its records and scattered stores, is slower at four: 219
+// against 187, and keeps one)
+constexpr int64_t kBruteShare = 65536;
+
+template <bool GEOM, int CPW>
 __global__ void __launch_bounds__(64) k_count_bf(NeighborArgs a)
 {
     __shared__ StructGeom gs;
-    const int64_t i = blockIdx.x;
-    const BruteCentre c = brute_centre<GEOM>(a, i, gs);
-    if (threadIdx.x == 0) {
-        if (!c.ok) put_status(a.status, SOAP_EINVAL);
-        const int sp = a.species[i];
-        if (sp < 0 || sp >= a.n_species) put_status(a.status, SOAP_ESPECIES);
+    BruteCentre c;
+    const int64_t first = int64_t(blockIdx.x) * CPW;
+    for (int64_t i = first; i < first + CPW && i < a.n_atoms; ++i) {
+        next_centre<GEOM>(a, i, i == first, c, gs);
+        if (threadIdx.x == 0) {
+            if (!c.ok) put_status(a.status, SOAP_EINVAL);
+            const int sp = a.species[i];
+            if (sp < 0 || sp >= a.n_species) put_status(a.status, SOAP_ESPECIES);
+        }
+        int n = 0;
+        brute_visit(a, i, c, gs, [&](bool hit, int, int, int, int, double, double, double) {
+            n += __popcll(__ballot(hit));
+        });
+        if (threadIdx.x == 0) a.centre_count[i] = n;
     }
-    int n = 0;
-    brute_visit(a, i, c, gs, [&](bool hit, int, int, int, int, double, double, double) { n += hit ? 1 : 0; });
-    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
-    if (threadIdx.x == 0) a.centre_count[i] = n;
 }
 
 // Offsets from all counts (without GEOM: N <= kBruteAtoms) or from the
@@ -1410,11 +1434,13 @@ hipError_t launch_neighbors(const NeighborArgs& a, hipStream_t stream)
     // kBrutePerStruct atoms: a 1024-atom cell is faster with bins)
     if (N <= kBrutePerStruct * int64_t(a.n_structures)) {
         const dim3 grid{unsigned(N)}, wave{64};
+        const dim3 grid4{unsigned(blocks(N, 4))};
+        const bool share = N >= kBruteShare;
         const bool self_check = N <= kBruteAtoms && a.n_structures <= kBruteStructs;
         if (self_check) {
             // each wave checks the input; with pairs to write the fill sums
             // the counts itself
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_count_bf<false>), grid, wave, 0, stream, a);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_count_bf<false, 1>), grid, wave, 0, stream, a);
             if (a.capacity > 0) {
                 if (a.vec_f64) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill_bf<false, true>), grid, wave, 0, stream, a);
                 else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_fill_bf<false, false>), grid, wave, 0, stream, a);
@@ -1422,7 +1448,8 @@ hipError_t launch_neighbors(const NeighborArgs& a, hipStream_t stream)
         } else {
             // many structures: the geometry phase, then the counts
             hipLaunchKernelGGL(k_geometry, dim3(1), dim3(1024), 0, stream, a);
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_count_bf<true>), grid, wave, 0, stream, a);
+            if (share) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_count_bf<true, 4>), grid4, wave, 0, stream, a);
+            else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_count_bf<true, 1>), grid, wave, 0, stream, a);
         }
         if (!self_check || a.capacity <= 0)   // offsets by a scan (which reports the count at capacity 0)
             scan<int64_t, int64_t>(a.centre_count, a.pair_offsets, (int64_t*)nullptr, N, a.capacity, a.scan_tmp,
