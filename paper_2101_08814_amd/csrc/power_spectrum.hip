@@ -103,29 +103,33 @@ __device__ __forceinline__ void tile(float* ob, int I, int J, int row, int kg, i
     }
 }
 
-// FP32 operands (v_mfma_f32_16x16x4_f32, one step per 4 of the 2l+1
-// values): lane (row, kg) supplies the values m = kg NS + s, s < NS =
-// ceil((2l+1) / 4), of row k of C_l (c_l points at m = 0 of row 0), so that
-// its NS reads are consecutive; A and B take the same order of m, which
-// leaves the product unchanged.  Zero past 2l+1 or K; rows past K read row
-// 0, and every read stays inside the region (padded by 32 words past C).
-__device__ __forceinline__ void row_operands_f32(const float* c_l, int k, int K, int L2, int w, int NS, int kg,
-                                                 float (&x)[kStepsF32])
+// FP32 operands (v_mfma_f32_16x16x4_f32, NS = ceil((2l+1) / 4) steps of 4 of
+// the 2l+1 values; a template parameter, so that a tile's reads are issued
+// together and its steps follow without a branch each): lane (row, kg)
+// supplies the values m = kg NS + s, s < NS, of row k of C_l (c_l points at
+// m = 0 of row 0), so that its NS reads are consecutive; A and B take the
+// same order of m, which leaves the product unchanged.  Zero past 2l+1; rows
+// past K read row 0 (their outputs are not stored), and every read stays
+// inside the region (padded by 32 words past C).
+template <int NS>
+__device__ __forceinline__ void row_operands_f32(const float* c_l, int k, int K, int L2, int w, int kg, float (&x)[NS])
 {
     const float* r = c_l + (k < K ? k : 0) * L2 + kg * NS;
 #pragma unroll
-    for (int s = 0; s < kStepsF32; ++s) x[s] = s < NS && kg * NS + s < w && k < K ? r[s] : 0.f;
+    for (int s = 0; s < NS; ++s) x[s] = r[s];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) x[s] = kg * NS + s < w ? x[s] : 0.f;
 }
 
 // The tile (I, J) of P_l = C_l C_l^T from FP32 operands, into the packed
 // upper triangle ob (the same output layout as the bfloat16 tile)
-__device__ __forceinline__ void tile_f32(float* ob, int I, int J, int row, int kg, int K, int NS,
-                                         const float (&xa)[kStepsF32], const float (&xb)[kStepsF32])
+template <int NS>
+__device__ __forceinline__ void tile_f32(float* ob, int I, int J, int row, int kg, int K, const float (&xa)[NS],
+                                         const float (&xb)[NS])
 {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < kStepsF32; ++s)
-        if (s < NS) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[s], xb[s], acc, 0, 0, 0);
+    for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[s], xb[s], acc, 0, 0, 0);
     const int k2 = J * 16 + row;
     int k1 = I * 16 + 4 * kg;
     int idx = k1 * K - k1 * (k1 - 1) / 2 + (k2 - k1);
@@ -134,6 +138,56 @@ __device__ __forceinline__ void tile_f32(float* ob, int I, int J, int row, int k
         if (k1 <= k2 && k2 < K) ob[idx] = acc[v];
         idx += K - k1 - 1;
         ++k1;
+    }
+}
+
+// All tiles of degree l that this wave owns, FP32 operands (as the bfloat16
+// form in the body below)
+template <int W, int NS>
+__device__ __forceinline__ void degree_f32(const float* c_l, float* ob, int K, int L2, int w, int T, int wc, int row,
+                                           int kg)
+{
+    if constexpr (W == 1) {
+        float rx[kRows1][NS];
+#pragma unroll
+        for (int I = 0; I < kRows1; ++I)
+            if (I < T) row_operands_f32<NS>(c_l, I * 16 + row, K, L2, w, kg, rx[I]);
+#pragma unroll
+        for (int I = 0; I < kRows1; ++I)
+#pragma unroll
+            for (int J = I; J < kRows1; ++J)
+                if (J < T) tile_f32<NS>(ob, I, J, row, kg, K, rx[I], rx[J]);
+    } else {
+        const int n_tiles = T * (T + 1) / 2;
+        const int per = (n_tiles + W - 1) / W;
+        const int t0 = wc * per, t1 = t0 + per < n_tiles ? t0 + per : n_tiles;
+        if (t0 >= t1) return;
+        int I = 0, rem = t0;
+        while (I < T && rem >= T - I) { rem -= T - I; ++I; }
+        int J = I + rem;
+        float xa[NS], xb[NS];
+        row_operands_f32<NS>(c_l, I * 16 + row, K, L2, w, kg, xa);
+        row_operands_f32<NS>(c_l, J * 16 + row, K, L2, w, kg, xb);
+        for (int t = t0;;) {
+            // the next tile's column operands are read during this tile
+            int I1 = I, J1 = J + 1;
+            if (J1 == T) {
+                ++I1;
+                J1 = I1;
+            }
+            const bool more = ++t < t1;
+            float xn[NS];
+            if (more) row_operands_f32<NS>(c_l, J1 * 16 + row, K, L2, w, kg, xn);
+            tile_f32<NS>(ob, I, J, row, kg, K, xa, xb);
+            if (!more) break;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                xb[s] = xn[s];
+                if (I1 != I) xa[s] = xn[s];   // a row starts on the diagonal
+            }
+            I = I1;
+            J = J1;
+        }
     }
 }
 
@@ -195,22 +249,22 @@ __device__ __forceinline__ void spectrum_body(const FeatureArgs& a)
         const unsigned int* hl_l = hl + l * l + kg * 8;
         float* dst = p_out + int64_t(l) * KK;
         // tiles (I, J), I <= J, row-major over the upper triangle
-        const int NS = (w + 3) / 4;   // FP32: 4-wide steps per product
         const float* c_l = reinterpret_cast<const float*>(hl) + l * l;
+        if constexpr (F32) {
+            switch ((w + 3) / 4) {
+            case 1: degree_f32<W, 1>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            case 2: degree_f32<W, 2>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            case 3: degree_f32<W, 3>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            case 4: degree_f32<W, 4>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            case 5: degree_f32<W, 5>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            case 6: degree_f32<W, 6>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            default: degree_f32<W, kStepsF32>(c_l, ob, K, L2, w, T, wc, row, kg); break;
+            }
+        } else
         if constexpr (W == 1) {
             // one wave: the operand values of every row block read once
             // (T <= kRows1), all reads issued before the first product
-            if constexpr (F32) {
-                float rx[kRows1][kStepsF32];
-#pragma unroll
-                for (int I = 0; I < kRows1; ++I)
-                    if (I < T) row_operands_f32(c_l, I * 16 + row, K, L2, w, NS, kg, rx[I]);
-#pragma unroll
-                for (int I = 0; I < kRows1; ++I)
-#pragma unroll
-                    for (int J = I; J < kRows1; ++J)
-                        if (J < T) tile_f32(ob, I, J, row, kg, K, NS, rx[I], rx[J]);
-            } else {
+            {
                 u16x8 rh[kRows1], rl[kRows1];
 #pragma unroll
                 for (int I = 0; I < kRows1; ++I)
@@ -230,20 +284,7 @@ __device__ __forceinline__ void spectrum_body(const FeatureArgs& a)
             int I = 0, rem = t0;
             while (I < T && rem >= T - I) { rem -= T - I; ++I; }
             int J = I + rem;
-            if constexpr (F32) {
-                float xa[kStepsF32];
-                if (t0 < t1) row_operands_f32(c_l, I * 16 + row, K, L2, w, NS, kg, xa);
-                for (int t = t0; t < t1; ++t) {
-                    float xb[kStepsF32];
-                    row_operands_f32(c_l, J * 16 + row, K, L2, w, NS, kg, xb);
-                    tile_f32(ob, I, J, row, kg, K, NS, xa, xb);
-                    if (++J == T && t + 1 < t1) {
-                        ++I;
-                        J = I;
-                        row_operands_f32(c_l, I * 16 + row, K, L2, w, NS, kg, xa);
-                    }
-                }
-            } else {
+            {
                 u16x8 ha, la;
                 if (t0 < t1) row_operands(hl_l, I * 16 + row, K, L2, nj, ha, la);
                 for (int t = t0; t < t1; ++t) {
