@@ -15,7 +15,9 @@
 // relative error of order 2^-16.
 //
 // W waves own one centre (W = 1, four centres per work-group, when C is
-// small and K <= 48; W = 4, one centre per work-group, otherwise): the
+// small and K <= 48; otherwise one centre per work-group, W = 4 up to K = 64
+// and W = 8 above, where the centre's LDS lets three work-groups share a CU:
+// 16,384 centres at K = 96, lmax 8: 851 -> 806 us): the
 // centre's waves split C into their LDS region as {H, L} pairs, then for
 // each l run the 16 x 16 output tiles (I <= J) as three
 // v_mfma_f32_16x16x32_bf16 each (a lane reads 8 consecutive {H, L} words
@@ -41,7 +43,8 @@ constexpr int kThreads = 256;
 constexpr int kLoadBatch = 16;   // coefficient loads a lane keeps in flight
 constexpr int kRows1 = 3;        // row blocks of 16 (K <= 48) a one-wave centre holds in registers
 constexpr int kStepsF32 = 7;     // 4-wide MFMA steps of a row of 2l+1 <= 25 values (lmax <= 12)
-constexpr int64_t kF32MfmaAtoms = 8192;   // FP32 spectra of at least this many centres use the matrix cores
+constexpr int64_t kF32MfmaAtoms = 8192;   // FP32 spectra of at least this many centres, or of at least
+constexpr int kF32MfmaK = 24;              // this many channels, use the matrix cores
 
 // round to nearest even (finite inputs)
 __device__ __forceinline__ unsigned short to_bf16(float f)
@@ -196,7 +199,7 @@ __device__ __forceinline__ void degree_f32(const float* c_l, float* ob, int K, i
 template <int W, bool F32>
 __device__ __forceinline__ void spectrum_body(const FeatureArgs& a)
 {
-    constexpr int CPG = kThreads / 64 / W;   // centres per work-group
+    constexpr int CPG = W > 4 ? 1 : 4 / W;   // centres per work-group
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int S = a.S, nmax = a.nmax, lmax = a.lmax;
     const int K = S * nmax, L2 = (lmax + 1) * (lmax + 1);
@@ -315,13 +318,13 @@ __device__ __forceinline__ void spectrum_body(const FeatureArgs& a)
 }
 
 template <int W>
-__global__ void __launch_bounds__(kThreads) k_power_spectrum_bf16(FeatureArgs a)
+__global__ void __launch_bounds__(W > 4 ? 64 * W : kThreads) k_power_spectrum_bf16(FeatureArgs a)
 {
     spectrum_body<W, false>(a);
 }
 
 template <int W>
-__global__ void __launch_bounds__(kThreads) k_power_spectrum_f32mfma(FeatureArgs a)
+__global__ void __launch_bounds__(W > 4 ? 64 * W : kThreads) k_power_spectrum_f32mfma(FeatureArgs a)
 {
     spectrum_body<W, true>(a);
 }
@@ -357,12 +360,12 @@ hipError_t launch_mfma(const FeatureArgs& a, size_t lds, hipStream_t stream)
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    constexpr int cpg = kThreads / 64 / W;
+    constexpr int cpg = W > 4 ? 1 : 4 / W, threads = W > 4 ? 64 * W : kThreads;
     const unsigned groups = unsigned((a.n_atoms + cpg - 1) / cpg);
     if constexpr (F32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_power_spectrum_f32mfma<W>), dim3(groups), dim3(kThreads), lds, stream, a);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_power_spectrum_f32mfma<W>), dim3(groups), dim3(threads), lds, stream, a);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_power_spectrum_bf16<W>), dim3(groups), dim3(kThreads), lds, stream, a);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_power_spectrum_bf16<W>), dim3(groups), dim3(threads), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -371,17 +374,18 @@ hipError_t launch_power_spectrum_f32mfma(const FeatureArgs& a, hipStream_t strea
     const size_t lds = power_spectrum_bf16_lds(a.S, a.nmax, a.lmax);
     if (lds > 160 * 1024 || a.lmax > 12) return hipErrorNotSupported;
     if (a.n_atoms == 0) return hipSuccess;
-    return bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1 ? launch_mfma<1, true>(a, lds, stream)
-                                                             : launch_mfma<4, true>(a, lds, stream);
+    if (bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1) return launch_mfma<1, true>(a, lds, stream);
+    return a.S * a.nmax > 64 ? launch_mfma<8, true>(a, lds, stream) : launch_mfma<4, true>(a, lds, stream);
 }
 
 hipError_t launch_power_spectrum(const FeatureArgs& a, soap_precision prec, hipStream_t stream)
 {
-    // FP32 without gradient rows from kF32MfmaAtoms centres on: FP32
-    // operands on the matrix cores (28,924 centres at K = 32: 165 -> 124 us,
-    // 131k at K = 96: 9.0 -> 6.9 ms); below, the VALU kernel (4096 centres
-    // at K = 20: 20 us against 24)
-    if (prec == SOAP_F32 && a.dp == nullptr && a.n_atoms >= kF32MfmaAtoms) {
+    // FP32 without gradient rows: FP32 operands on the matrix cores.  Against
+    // the VALU kernel, at K = 96 (lmax 8) 100 centres take 22 against 74 us,
+    // 4096 217 against 374; K = 64 (lmax 6) 1000 centres 23 against 34; K = 24
+    // 4096 centres 17 against 21; at K = 20 (lmax 8) 4096 centres 22.2 against
+    // 21.4, so fewer channels wait for kF32MfmaAtoms centres.
+    if (prec == SOAP_F32 && a.dp == nullptr && (a.n_atoms >= kF32MfmaAtoms || a.S * a.nmax >= kF32MfmaK)) {
         const hipError_t e = launch_power_spectrum_f32mfma(a, stream);
         if (e != hipErrorNotSupported) return e;
     }
@@ -389,8 +393,8 @@ hipError_t launch_power_spectrum(const FeatureArgs& a, soap_precision prec, hipS
     const size_t lds = power_spectrum_bf16_lds(a.S, a.nmax, a.lmax);
     if (lds > 160 * 1024) return hipErrorNotSupported;
     if (a.n_atoms == 0) return hipSuccess;
-    return bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1 ? launch_mfma<1, false>(a, lds, stream)
-                                                             : launch_mfma<4, false>(a, lds, stream);
+    if (bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1) return launch_mfma<1, false>(a, lds, stream);
+    return a.S * a.nmax > 64 ? launch_mfma<8, false>(a, lds, stream) : launch_mfma<4, false>(a, lds, stream);
 }
 
 }  // namespace soap
