@@ -12,6 +12,21 @@
 // (grad Y_lm = (grad Z_lm - l Y_lm u) / r).  Nothing per pair is staged and
 // no lane decodes an index; the per-atom sums stay in the gather kernel of
 // backward.hip.
+//
+// The cubics come a group of two at a time, the next group loading meanwhile,
+// and the reads of G of a group's two rows go out together.  4096 centres of
+// some 70 pairs at n=10, lmax=8 took 60 us with single cubics two ahead, and
+// the wave waiting 55% of its cycles; 51 now, 33 of it vector instructions
+// (at lmax 8 the launch bound keeps the second wave a SIMD: 79 us without).
+//
+// Where the registers leave one wave a SIMD, a chunk of at most 32 pairs gives
+// each pair two lanes, 32 apart, each with half of the n: A, B and the five
+// sums are linear in G, so the halves add at the end, and only the harmonics
+// are formed twice.  1024 centres of 28 pairs at n=10, lmax=12 took 48 us,
+// 42 with the groups, 32 with the halves (at lmax 9 29, 24 and 20; in double
+// at lmax 8 36, 33 and 25).  At lower degrees, where two waves and more hide
+// each other's waits, the halves gain less (26.6, 22.1 and 19.1 at lmax 8 in
+// float) and one lane keeps the order of the sum over n.
 #include "lane_pair.hpp"
 
 namespace soap {
@@ -19,11 +34,21 @@ namespace {
 
 using namespace dev;
 
+__device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+__device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
+
+// The degrees above which the registers leave one wave a SIMD.
+template <typename T>
+constexpr bool one_wave(int lmax) { return lmax > (sizeof(T) == 4 ? 8 : 5); }
+
 template <typename T, int LMAX>
-__global__ void __launch_bounds__(64) k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c,
-                                                           T* __restrict__ grad_pair)
+__global__ void __launch_bounds__(64, one_wave<T>(LMAX) ? 1 : 2)
+k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c, T* __restrict__ grad_pair)
 {
     constexpr int LM1 = LMAX + 1, L2 = LM1 * LM1;
+    // cubics per group (of 1, 2, 3 and 4 the fastest in float; in double two
+    // cost the second wave where there is one)
+    constexpr int GR = sizeof(T) == 4 || one_wave<T>(LMAX) ? 2 : 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* G = reinterpret_cast<T*>(smem_raw);
     const int lane = threadIdx.x;
@@ -50,20 +75,28 @@ __global__ void __launch_bounds__(64) k_exp_backward_lanes(FeatureArgs a, const 
     const V4<T>* __restrict__ coef = static_cast<const V4<T>*>(a.coef_ln);
     const T* __restrict__ vec = static_cast<const T*>(a.pair_vec);
     const T inv_delta = T(a.inv_delta);
-    for (int64_t q0 = qb; q0 < qe; q0 += 64) {
-        const int64_t q = q0 + lane;
-        if (q >= qe) continue;
-        const PairGeom<T> g = pair_geometry<T>(a, vec[3 * q], vec[3 * q + 1], vec[3 * q + 2]);
-        const int sp = pair_species(a, q);
-        const T* Gs = G + sp * nL2;
-        const V4<T>* cf = coef + int64_t(g.k) * (LM1 * nmax);
+    // pairs q0 .. q0 + np - 1, one lane each or (SPLIT) two
+    auto chunk = [&](auto Split, int64_t q0, int np) __attribute__((always_inline)) {
+        constexpr bool SPLIT = decltype(Split)::value;
+        const int p = SPLIT ? lane & 31 : lane;
+        const int64_t q = q0 + p;
+        const bool live = p < np;
+        const int64_t qq = live ? q : q0;   // the lanes past the chunk follow its first pair and write nothing
+        const PairGeom<T> g = pair_geometry<T>(a, vec[3 * qq], vec[3 * qq + 1], vec[3 * qq + 2]);
+        const int sp = pair_species(a, qq);
+        // this lane's n: nb .. nb + cnt - 1 below nmax
+        const int cnt = SPLIT ? (nmax + 1) >> 1 : nmax, nb = SPLIT && lane >= 32 ? cnt : 0;
+        const T t3 = T(3) * g.t;
+        const int full = SPLIT ? nmax >> 1 : nmax;   // both halves have that many
+        const T* Gs = G + sp * nL2 + nb * L2;
+        const V4<T>* cf = coef + int64_t(g.k) * (LM1 * nmax) + nb;
         YlmStream<T, LMAX> ys(g.ux, g.uy, g.uz);
         T sA = T(0), sL = T(0), tx = T(0), ty = T(0), tz = T(0);
-        // the interval's cubics are contiguous ([l][n]); they stream two
-        // ahead of their use, across degrees (the table has zero entries past
-        // its end for the last ones)
-        V4<T> c0 = cf[0], c1 = cf[1];
-        const V4<T>* cnext = cf + 2;
+        // the interval's cubics are contiguous ([l][n]; past a degree's end
+        // the next one's, past the table's end its zeros, not used)
+        V4<T> nxt[GR];
+#pragma unroll
+        for (int u = 0; u < GR; ++u) nxt[u] = cf[u];
         static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
             constexpr int L = decltype(Lc)::value;
             constexpr int NM = 2 * L + 1;
@@ -71,20 +104,38 @@ __global__ void __launch_bounds__(64) k_exp_backward_lanes(FeatureArgs a, const 
 #pragma unroll
             for (int m = 0; m < NM; ++m) A[m] = B[m] = T(0);
             const T* gr = Gs + L * L;
-            for (int n = 0; n < nmax; ++n) {
-                const V4<T> c = c0;
-                c0 = c1;
-                c1 = *cnext++;
-                T v, dv;
-                spline_poly<T>(c.x, c.y, c.z, c.w, g.t, inv_delta, v, dv);
-                const T R = g.f * v, dR = g.df * v + g.f * dv;
+            for (int k0 = 0; k0 < cnt; k0 += GR) {
+                V4<T> cur[GR];
 #pragma unroll
-                for (int m = 0; m < NM; ++m) {
-                    const T gv = gr[m];
-                    A[m] += gv * dR;
-                    B[m] += gv * R;
+                for (int u = 0; u < GR; ++u) cur[u] = nxt[u];
+                if (k0 + GR < cnt || L < LMAX) {
+                    const V4<T>* nx = cf + (k0 + GR < cnt ? L * nmax + k0 + GR : (L + 1) * nmax);
+#pragma unroll
+                    for (int u = 0; u < GR; ++u) nxt[u] = nx[u];
                 }
-                gr += L2;
+                auto add = [&](int u) __attribute__((always_inline)) {
+                    const V4<T> c = cur[u];
+                    // the spline's value and slope with every rounding pinned,
+                    // whichever way the loop around it is unrolled
+                    const T v = fma_(g.t, fma_(g.t, fma_(g.t, c.w, c.z), c.y), c.x);
+                    const T dv = fma_(g.t, fma_(T(2), c.z, t3 * c.w), c.y) * inv_delta;
+                    const T R = g.f * v, dR = fma_(g.f, dv, g.df * v);
+                    const T* gu = gr + (k0 + u) * L2;
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        const T gv = gu[m];
+                        A[m] = fma_(gv, dR, A[m]);
+                        B[m] = fma_(gv, R, B[m]);
+                    }
+                };
+                if (k0 + GR <= full) {
+#pragma unroll
+                    for (int u = 0; u < GR; ++u) add(u);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < GR; ++u)
+                        if (k0 + u < cnt && (!SPLIT || nb + k0 + u < nmax)) add(u);
+                }
             }
             T sB = T(0);
             ys.template degree<L, true>([&](int mi, T Y, T zx, T zy, T zz) __attribute__((always_inline)) {
@@ -96,10 +147,29 @@ __global__ void __launch_bounds__(64) k_exp_backward_lanes(FeatureArgs a, const 
             });
             sL += T(L) * sB;
         });
+        if (SPLIT) {
+            sA += __shfl_xor(sA, 32, 64);
+            sL += __shfl_xor(sL, 32, 64);
+            tx += __shfl_xor(tx, 32, 64);
+            ty += __shfl_xor(ty, 32, 64);
+            tz += __shfl_xor(tz, 32, 64);
+        }
         const T radial = sA - sL * g.rinv;
-        grad_pair[3 * q] = g.ux * radial + tx * g.rinv;
-        grad_pair[3 * q + 1] = g.uy * radial + ty * g.rinv;
-        grad_pair[3 * q + 2] = g.uz * radial + tz * g.rinv;
+        if (live && (!SPLIT || lane < 32)) {
+            grad_pair[3 * q] = g.ux * radial + tx * g.rinv;
+            grad_pair[3 * q + 1] = g.uy * radial + ty * g.rinv;
+            grad_pair[3 * q + 2] = g.uz * radial + tz * g.rinv;
+        }
+    };
+    for (int64_t q0 = qb; q0 < qe; q0 += 64) {
+        const int np = qe - q0 < 64 ? int(qe - q0) : 64;
+        if constexpr (one_wave<T>(LMAX)) {
+            if (np <= 32 && nmax > 1) {
+                chunk(std::true_type{}, q0, np);
+                continue;
+            }
+        }
+        chunk(std::false_type{}, q0, np);
     }
 }
 
