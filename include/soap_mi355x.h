@@ -481,11 +481,10 @@ soap_status soap_compress_forward(const soap_calculator* calc, const soap_exec* 
  * soap_compress_workspace_size bytes.  With SOAP_BF16_F32ACC (and the
  * shapes of the one-wave-per-centre kernel: K, hidden <= 128 and multiples
  * of 4, n_out <= 32, 1 <= lmax <= 12) the weights are first laid out once in
- * the workspace as the kernel holds them in LDS (bfloat16 rows, the same
- * rounding), and each work-group copies the next degree's image while it
- * computes the current one; the results are those of soap_compress_forward
- * bit for bit.  The workspace is overwritten; calls that overlap must not
- * share it.                                                             */
+ * the workspace as the operands of the matrix instructions (bfloat16, the
+ * same rounding), which every wave reads from there, and c of a centre is
+ * read once; the results are those of soap_compress_forward bit for bit.
+ * The workspace is overwritten; calls that overlap must not share it.   */
 soap_status soap_compress_forward_ws(const soap_calculator* calc, const soap_exec* exec, soap_precision precision,
                                      int32_t n_out, int32_t hidden, int64_t n_atoms, const float* weights,
                                      const float* coeffs, float* coeffs_out, float* p_out, void* workspace,
