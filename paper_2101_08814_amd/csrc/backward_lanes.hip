@@ -34,9 +34,6 @@ namespace {
 
 using namespace dev;
 
-__device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
-__device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
-
 // The degrees above which the registers leave one wave a SIMD.
 template <typename T>
 constexpr bool one_wave(int lmax) { return lmax > (sizeof(T) == 4 ? 8 : 5); }

@@ -1,9 +1,9 @@
-// Spherical expansion (and power spectrum) with one lane per pair.
+// Spherical expansion (and power spectrum) of a centre by one wave.
 //
 // Expansion (Sec. 4.A Eq. spherical_expansion_coefficients_gaussians, Sec.
 // 4.F), k_expansion_lanes: one wave per centre.  For a chunk of up to 64 of
-// its pairs, lane p forms pair p's harmonics Y_lm and radial values
-// R_nl = f I~_nl in registers and puts them in the wave's LDS rows; then
+// its pairs, one to four lanes per pair form its harmonics Y_lm and radial
+// values R_nl = f I~_nl in registers and put them in the wave's LDS rows; then
 // each lane owns items (four n, one lm) of a species block and sums
 // R_{n..n+3,l} Y_lm over the pairs of that species (one 16-byte and one
 // 4-byte LDS read per four FMAs).  Pairs arrive grouped by neighbour species
@@ -42,7 +42,6 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     const int NI = ((nmax + 3) >> 2) * L2;
     const int nl = LM1 * nmax;
     const int64_t qb = a.pair_offsets[i], qe = a.pair_offsets[i + 1];
-    const int n_chunks = int((qe - qb + W.ch - 1) / W.ch);
     const T* __restrict__ centre_term = static_cast<const T*>(a.center);
     const V4<T>* __restrict__ coef = static_cast<const V4<T>*>(a.coef_ln);
     const T* __restrict__ vec = static_cast<const T*>(a.pair_vec);
@@ -118,61 +117,79 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
         zero_block(cs4);
     }
 
-    // lane p < nc stages pair q0 + p (harmonics and radial values in its
-    // LDS rows) and returns its neighbour's species (-1 past the chunk).
-    // The radial values j = l nmax + n of the pair's interval are
-    // contiguous in the table: they stream in batches of eight with two
-    // batches in flight, one batch consumed after each degree of harmonics.
-    // The table has 32 zero entries past its end and each LDS row spare
-    // elements for the rest of the last batch, so the last batches read and
-    // write past the pair's values without a bounds check.
-    // LDS offset of radial value j = l nmax + n in the rows [l][np]:
-    // j + l (np - nmax), l = floor(j / nmax) = (j * ceil(2^16 / nmax)) >> 16
-    // (exact for j < 2^12)
-    const int rpad = W.np - nmax, rmul = (65536 + nmax - 1) / nmax;
+    // Stages pairs q0 .. q0 + nc - 1 (harmonics and radial values in their
+    // LDS rows); lane p < nc returns pair p's neighbour's species (the other
+    // lanes' values mean nothing).  A pair takes 64 / 2^ceil(log2 nc) lanes side by side, at most
+    // four: all of them run the harmonics (the first writes them), and each
+    // forms its share of the radial values, so that a chunk of few pairs does
+    // not leave most of the wave idle along one lane's chain of loads.
+    // The radial values are formed four n at a time: quad j = l G + n / 4 of
+    // the G = np / 4 quads of every degree sits at 4 j of the pair's row
+    // [l][np], its cubics at 4 j - l (np - nmax) of the interval's block
+    // [l][nmax] (l = (j ceil(2^16 / G)) >> 16, exact for j < 2^12).  They
+    // stream with two quads in flight, one consumed after each degree of
+    // harmonics.  The quad of a degree's end may run into the next degree's
+    // cubics, or the table's 32 zero entries past its end; what it puts past
+    // nmax is not used.
+    // One lane per pair with two batches of eight values took 38.2 us for
+    // 1024 centres of 28 pairs at n=10, lmax=12 (chunks of 16 pairs by LDS),
+    // 30.3 now, and 63.6 and 46.9 for 2048 centres of 45 pairs at n=10,
+    // lmax=8, where the chunks of 32 take the wave's two halves; two quads
+    // a step: 31.9 and 49.7, three: 33.7 and 50.4.
+    const int rpad = W.np - nmax, G = W.np >> 2, QN = LM1 * G, rmul = (65536 + G - 1) / G;
     auto stage = [&](int64_t q0, int nc) __attribute__((always_inline)) -> int {
         int my_sp = -1;
-        if (lane < nc) {
-            const int64_t q = q0 + lane;
+        const int sh = nc <= 16 ? 2 : nc <= 32 ? 1 : 0;
+        const int p = lane >> sh, part = lane & ((1 << sh) - 1);
+        if (p < nc) {
+            const int64_t q = q0 + p;
             const PairGeom<T> g = pair_geometry<T>(a, vec[3 * q], vec[3 * q + 1], vec[3 * q + 2]);
             my_sp = pair_species(a, q);
             const V4<T>* cf = coef + int64_t(g.k) * nl;
-            T* yrow = Ys + lane * W.l2s;
-            T* rrow = Rs + lane * W.nls;
-            const T tt = g.t, f = g.f;
-            V4<T> A[8], B[8];
+            T* yrow = Ys + p * W.l2s;
+            T* rrow = Rs + p * W.nls;
+            // (the place in the interval with one rounding, whatever is around it)
+            const T tt = fma_(g.r, T(a.inv_delta), -T(g.k)), f = g.f;
+            // quad j, or quad 0 past the last one
+            auto load = [&](V4<T>* c, int j) __attribute__((always_inline)) {
+                const int jj = j < QN ? j : 0;
+                const V4<T>* cj = cf + 4 * jj - rpad * ((jj * rmul) >> 16);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                A[u] = cf[u];
-                B[u] = cf[8 + u];
-            }
-            int jb = 0;
+                for (int u = 0; u < 4; ++u) c[u] = cj[u];
+            };
+            const int step = 1 << sh;
+            V4<T> A[4], B[4];
+            load(A, part);
+            load(B, part + step);
+            int jb = 0;   // the first of the quads that the pair's lanes take now
             auto consume = [&]() __attribute__((always_inline)) {
-                // jb opaque here: the offsets of each batch are formed where
-                // they are used instead of all at once at the kernel start
-                asm volatile("" : "+s"(jb));
+                const int j = jb + part;
+                T v[4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const T v = f * (A[u].x + tt * (A[u].y + tt * (A[u].z + tt * A[u].w)));
-                    const int j = jb + u;
-                    rrow[j + rpad * ((j * rmul) >> 16)] = v;
+                for (int u = 0; u < 4; ++u) {
+                    const V4<T> c = A[u];
+                    v[u] = f * (c.x + tt * (c.y + tt * (c.z + tt * c.w)));
                     A[u] = B[u];
-                    B[u] = cf[jb + 16 + u];
                 }
-                jb += 8;
+                load(B, j + 2 * step);
+                if (j < QN) *reinterpret_cast<V4<T>*>(rrow + 4 * j) = V4<T>{v[0], v[1], v[2], v[3]};
+                jb += step;
             };
             YlmStream<T, LMAX> ys(g.ux, g.uy, g.uz);
             static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
                 constexpr int L = decltype(Lc)::value;
-                ys.template degree<L, false>([&](int mi, T Y, T, T, T) __attribute__((always_inline)) {
-                    yrow[L * L + mi] = Y;
-                });
-                if (jb < nl) consume();
+                T Yd[2 * L + 1];
+                ys.template degree<L, false>([&](int mi, T Y, T, T, T) __attribute__((always_inline)) { Yd[mi] = Y; });
+                if (part == 0) {
+#pragma unroll
+                    for (int m = 0; m < 2 * L + 1; ++m) yrow[L * L + m] = Yd[m];
+                }
+                if (jb < QN) consume();
             });
-            while (jb < nl) consume();
+            while (jb < QN) consume();
         }
         wave_sync();
-        return my_sp;
+        return __shfl(my_sp, (lane << sh) & 63, 64);
     };
 
     // Grouped pass: blocks written as the species changes.  A chunk whose
@@ -180,8 +197,7 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     // the centre as not grouped.
     int cur = 0;
     bool grouped = true;
-    for (int ck = 0; ck < n_chunks && grouped; ++ck) {
-        const int64_t q0 = qb + int64_t(ck) * W.ch;
+    for (int64_t q0 = qb; q0 < qe && grouped; q0 += W.ch) {
         const int nc = int(qe - q0 < W.ch ? qe - q0 : W.ch);
         const int my_sp = stage(q0, nc);
         const int prev = __shfl_up(my_sp, 1, 64);
@@ -212,8 +228,7 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
             zero_block(cs4);
         }
         for (int sp = 0; sp < S; ++sp) {
-            for (int ck = 0; ck < n_chunks; ++ck) {
-                const int64_t q0 = qb + int64_t(ck) * W.ch;
+            for (int64_t q0 = qb; q0 < qe; q0 += W.ch) {
                 const int nc = int(qe - q0 < W.ch ? qe - q0 : W.ch);
                 const int my_sp = stage(q0, nc);
                 for (int p = 0; p < nc; ++p)
