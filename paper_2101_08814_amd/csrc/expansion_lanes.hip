@@ -1,10 +1,10 @@
-// Spherical expansion (and power spectrum) of a centre by one wave.
+// Spherical expansion (and power spectrum) of a centre by one to four waves.
 //
 // Expansion (Sec. 4.A Eq. spherical_expansion_coefficients_gaussians, Sec.
-// 4.F), k_expansion_lanes: one wave per centre.  For a chunk of up to 64 of
-// its pairs, one to four lanes per pair form its harmonics Y_lm and radial
-// values R_nl = f I~_nl in registers and put them in the wave's LDS rows; then
-// each lane owns items (four n, one lm) of a species block and sums
+// 4.F), k_expansion_lanes: one work-group of one, two or four waves per
+// centre.  For a chunk of up to 64 of its pairs, one to sixteen lanes per
+// pair form its harmonics Y_lm and radial values R_nl = f I~_nl in registers
+// and put them in the centre's LDS rows; then each lane owns items (four n, one lm) of a species block and sums
 // R_{n..n+3,l} Y_lm over the pairs of that species (one 16-byte and one
 // 4-byte LDS read per four FMAs).  Pairs arrive grouped by neighbour species
 // (the order soap_compute_neighbors writes), so a block is complete when the
@@ -22,8 +22,8 @@ namespace {
 using namespace dev;
 
 // ------------------------------------------------------------- expansion
-template <typename T, int LMAX, bool WANT_P>
-__global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayout W)
+template <typename T, int LMAX, bool WANT_P, int NW>
+__global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, LaneLayout W)
 {
     constexpr int LM1 = LMAX + 1, L2 = LM1 * LM1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -31,10 +31,15 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     T* Rs = base + W.rs;
     T* Ys = base + W.ys;
     T* Cs = base + W.cs;
-    const int lane = threadIdx.x;
+    constexpr int NT = 64 * NW;
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto sync = [&]() __attribute__((always_inline)) {
+        if constexpr (NW == 1) wave_sync();
+        else __syncthreads();
+    };
     const int64_t i = blockIdx.x;
     if (a.pair_offsets[a.n_atoms] > a.pair_capacity) {
-        if (lane == 0) put_status(a.status, SOAP_ECAPACITY);
+        if (tid == 0) put_status(a.status, SOAP_ECAPACITY);
         return;
     }
     const int nmax = a.nmax, S = a.S;
@@ -49,7 +54,7 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     if (a.include_center) {
         sp_i = a.species[i];
         if (sp_i < 0 || sp_i >= S) {
-            if (lane == 0) put_status(a.status, SOAP_ESPECIES);
+            if (tid == 0) put_status(a.status, SOAP_ESPECIES);
             sp_i = -1;
         }
     }
@@ -61,7 +66,7 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     V4<T>* const cs4 = reinterpret_cast<V4<T>*>(Cs);
     auto block = [&](int sp) __attribute__((always_inline)) { return cs4 + (WANT_P ? sp * NI : 0); };
     auto zero_block = [&](V4<T>* blk) __attribute__((always_inline)) {
-        for (int v = lane; v < NI; v += 64) blk[v] = V4<T>{T(0), T(0), T(0), T(0)};
+        for (int v = tid; v < NI; v += NT) blk[v] = V4<T>{T(0), T(0), T(0), T(0)};
     };
     // species block sp of c to HBM with consecutive lanes on consecutive
     // addresses; the central atom adds its term to lm = 0 of its own species
@@ -69,10 +74,10 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     auto flush = [&](int sp) __attribute__((always_inline)) {
         V4<T>* blk = block(sp);
         T* b1 = reinterpret_cast<T*>(blk);
-        wave_sync();
+        sync();
         T* dst = c_out + sp * nL2;
         const bool own = sp == sp_i;
-        for (int e = lane; e < nL2; e += 64) {
+        for (int e = tid; e < nL2; e += NT) {
             const int n = e / L2, lm = e - n * L2;
             T* src = b1 + ((n >> 2) * L2 + lm) * 4 + (n & 3);
             T v = *src;
@@ -82,17 +87,17 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
             }
             dst[e] = v;
         }
-        wave_sync();
+        sync();
         if (!WANT_P) {
             zero_block(blk);
-            wave_sync();
+            sync();
         }
     };
     // the chunk's pairs [lo, hi) of species sp added to its block: per item
     // and pair one 4-byte and one 16-byte LDS read and four FMAs
     auto accumulate = [&](int sp, int lo, int hi) __attribute__((always_inline)) {
         V4<T>* blk = block(sp);
-        for (int v = lane; v < NI; v += 64) {
+        for (int v = tid; v < NI; v += NT) {
             const int ng = v / L2, lm = v - ng * L2;
             V4<T> s4 = blk[v];
             const T* yp = Ys + lo * W.l2s + lm;
@@ -112,17 +117,18 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
         }
     };
     if (WANT_P) {
-        for (int v = lane; v < S * NI; v += 64) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
+        for (int v = tid; v < S * NI; v += NT) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
     } else {
         zero_block(cs4);
     }
 
     // Stages pairs q0 .. q0 + nc - 1 (harmonics and radial values in their
-    // LDS rows); lane p < nc returns pair p's neighbour's species (the other
-    // lanes' values mean nothing).  A pair takes 64 / 2^ceil(log2 nc) lanes side by side, at most
-    // four: all of them run the harmonics (the first writes them), and each
-    // forms its share of the radial values, so that a chunk of few pairs does
-    // not leave most of the wave idle along one lane's chain of loads.
+    // LDS rows); lane p < nc of every wave returns pair p's neighbour's
+    // species (the other lanes' values mean nothing).  A pair takes one, two
+    // or four lanes per wave, side by side: all of them run the harmonics (the
+    // first writes them), and each forms its share of the radial values, so
+    // that a chunk of few pairs does not leave most of the wave idle along one
+    // lane's chain of loads.
     // The radial values are formed four n at a time: quad j = l G + n / 4 of
     // the G = np / 4 quads of every degree sits at 4 j of the pair's row
     // [l][np], its cubics at 4 j - l (np - nmax) of the interval's block
@@ -133,18 +139,17 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     // nmax is not used.
     // One lane per pair with two batches of eight values took 38.2 us for
     // 1024 centres of 28 pairs at n=10, lmax=12 (chunks of 16 pairs by LDS),
-    // 30.3 now, and 63.6 and 46.9 for 2048 centres of 45 pairs at n=10,
-    // lmax=8, where the chunks of 32 take the wave's two halves; two quads
-    // a step: 31.9 and 49.7, three: 33.7 and 50.4.
+    // with the shares of one wave 30.2, and 63.6 and 46.9 for 2048 centres of
+    // 45 pairs at n=10, lmax=8, where the chunks of 32 take the wave's two
+    // halves; two quads a step: 31.9 and 49.7, three: 33.7 and 50.4.
     const int rpad = W.np - nmax, G = W.np >> 2, QN = LM1 * G, rmul = (65536 + G - 1) / G;
     auto stage = [&](int64_t q0, int nc) __attribute__((always_inline)) -> int {
-        int my_sp = -1;
-        const int sh = nc <= 16 ? 2 : nc <= 32 ? 1 : 0;
-        const int p = lane >> sh, part = lane & ((1 << sh) - 1);
+        constexpr int W0 = NW == 4 ? 2 : NW == 2 ? 1 : 0;
+        const int sh = W0 + (nc <= 16 ? 2 : nc <= 32 ? 1 : 0);
+        const int p = tid >> sh, part = tid & ((1 << sh) - 1);
         if (p < nc) {
             const int64_t q = q0 + p;
             const PairGeom<T> g = pair_geometry<T>(a, vec[3 * q], vec[3 * q + 1], vec[3 * q + 2]);
-            my_sp = pair_species(a, q);
             const V4<T>* cf = coef + int64_t(g.k) * nl;
             T* yrow = Ys + p * W.l2s;
             T* rrow = Rs + p * W.nls;
@@ -188,8 +193,9 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
             });
             while (jb < QN) consume();
         }
-        wave_sync();
-        return __shfl(my_sp, (lane << sh) & 63, 64);
+        const int my_sp = pair_species(a, q0 + (lane < nc ? lane : 0));   // the same in every wave
+        sync();
+        return my_sp;
     };
 
     // Grouped pass: blocks written as the species changes.  A chunk whose
@@ -216,14 +222,14 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
             accumulate(sp, lo, lo + cnt);
             lo += cnt;
         }
-        wave_sync();
+        sync();
     }
     if (grouped) {
         for (int sp = cur; sp < S; ++sp) flush(sp);
     } else {
         // pairs not grouped by species: every block, one species per pass
         if (WANT_P) {
-            for (int v = lane; v < S * NI; v += 64) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
+            for (int v = tid; v < S * NI; v += NT) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
         } else {
             zero_block(cs4);
         }
@@ -233,16 +239,16 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
                 const int my_sp = stage(q0, nc);
                 for (int p = 0; p < nc; ++p)
                     if (__builtin_amdgcn_readlane(my_sp, p) == sp) accumulate(sp, p, p + 1);
-                wave_sync();
+                sync();
             }
             flush(sp);
         }
     }
     if constexpr (WANT_P) {
-        wave_sync();
+        sync();
         const int K = S * nmax, KK = K * (K + 1) / 2;
         T* p_out = static_cast<T*>(a.p) + i * int64_t(LM1 * KK);
-        for (int kk = lane; kk < KK; kk += 64) {
+        for (int kk = tid; kk < KK; kk += NT) {
             int k1, k2;
             tri_decode(K, kk, k1, k2);
             // c_{k, lm} sits at ((ng L2 + lm) 4 + n % 4) of species a's block
@@ -260,6 +266,32 @@ __global__ void __launch_bounds__(64) k_expansion_lanes(FeatureArgs a, LaneLayou
     }
 }
 
+template <typename T, int LM, bool WANT_P, int NW>
+hipError_t launch_lanes(const FeatureArgs& a, const LaneLayout& W, hipStream_t st)
+{
+    const size_t lds = size_t(W.total) * sizeof(T);
+    auto kernel = k_expansion_lanes<T, LM, WANT_P, NW>;
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_atoms)), dim3(64 * NW), lds, st, a, W);
+    return hipGetLastError();
+}
+
+// Waves per centre for c and p: with one, fewer than 4096 centres leave most
+// of the chip's waves empty and each centre's sums and products run as one
+// chain.  Two are faster than one at every size measured (4000 centres of 45
+// pairs at n=10, lmax=8: 85 and 72 us, double 190 and 165; 1024 of 28 at
+// n=10, lmax=12: 30.2 and 25.8), four only while a CU has few centres: 21
+// centres of four species at n=8, lmax=6 take 19.0 us with one, 13.4 with two
+// and 11.2 with four, 512 float ones at n=9, lmax=6 15.8, 12.5 and 10.2, but
+// 512 in double at n=6, lmax=4 10.8, 10.0 and 10.3, and the 1024 above 33.2.
+// c alone comes here only for shapes that the packed kernel does not take,
+// at any number of centres: one wave.
+constexpr int64_t kFourWavesBytes = 2048;   // four waves up to that many centres times the element's size
+
 template <typename T, int LM>
 struct LanesFn {
     static hipError_t run(const FeatureArgs& a, const LaneLayout& W, bool want_p, hipStream_t st)
@@ -267,20 +299,9 @@ struct LanesFn {
         if constexpr (LM < 0) {
             return hipErrorNotSupported;
         } else {
-            const size_t lds = size_t(W.total) * sizeof(T);
-            const void* fn = want_p ? reinterpret_cast<const void*>(k_expansion_lanes<T, LM, true>)
-                                    : reinterpret_cast<const void*>(k_expansion_lanes<T, LM, false>);
-            if (lds > 65536) {
-                hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-                if (e != hipSuccess) return e;
-            }
-            if (want_p)
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_expansion_lanes<T, LM, true>), dim3(unsigned(a.n_atoms)),
-                                   dim3(64), lds, st, a, W);
-            else
-                hipLaunchKernelGGL(HIP_KERNEL_NAME(k_expansion_lanes<T, LM, false>), dim3(unsigned(a.n_atoms)),
-                                   dim3(64), lds, st, a, W);
-            return hipGetLastError();
+            if (!want_p) return launch_lanes<T, LM, false, 1>(a, W, st);
+            return a.n_atoms * int64_t(sizeof(T)) <= kFourWavesBytes ? launch_lanes<T, LM, true, 4>(a, W, st)
+                                                                     : launch_lanes<T, LM, true, 2>(a, W, st);
         }
     }
 };
