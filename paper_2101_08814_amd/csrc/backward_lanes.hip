@@ -114,15 +114,15 @@ k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c, T* __restrict_
                     const V4<T> c = cur[u];
                     // the spline's value and slope with every rounding pinned,
                     // whichever way the loop around it is unrolled
-                    const T v = fma_(g.t, fma_(g.t, fma_(g.t, c.w, c.z), c.y), c.x);
-                    const T dv = fma_(g.t, fma_(T(2), c.z, t3 * c.w), c.y) * inv_delta;
-                    const T R = g.f * v, dR = fma_(g.f, dv, g.df * v);
+                    const T v = fma(g.t, fma(g.t, fma(g.t, c.w, c.z), c.y), c.x);
+                    const T dv = fma(g.t, fma(T(2), c.z, t3 * c.w), c.y) * inv_delta;
+                    const T R = g.f * v, dR = fma(g.f, dv, g.df * v);
                     const T* gu = gr + (k0 + u) * L2;
 #pragma unroll
                     for (int m = 0; m < NM; ++m) {
                         const T gv = gu[m];
-                        A[m] = fma_(gv, dR, A[m]);
-                        B[m] = fma_(gv, R, B[m]);
+                        A[m] = fma(gv, dR, A[m]);
+                        B[m] = fma(gv, R, B[m]);
                     }
                 };
                 if (k0 + GR <= full) {

@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
             T* yrow = Ys + p * W.l2s;
             T* rrow = Rs + p * W.nls;
             // (the place in the interval with one rounding, whatever is around it)
-            const T tt = fma_(g.r, T(a.inv_delta), -T(g.k)), f = g.f;
+            const T tt = fma(g.r, T(a.inv_delta), -T(g.k)), f = g.f;
             // quad j, or quad 0 past the last one
             auto load = [&](V4<T>* c, int j) __attribute__((always_inline)) {
                 const int jj = j < QN ? j : 0;
@@ -358,8 +358,9 @@ hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t st
         if (e != hipErrorNotSupported) return e;
     } else if (a.n_atoms >= kSplitAtoms) {
         // c with the pairs packed across centres, then p from c in HBM
-        // (4096-atom liquid: 86 us against 113 for c and p in one kernel;
-        // smaller systems are faster in one launch)
+        // (4096 liquid centres: 61 and 21 us against 78 for c and p in one
+        // kernel, 8000 90 and 33 against 126; at n=6, lmax=4 in double 23 and
+        // 9 against 39; smaller systems are faster in one launch)
         FeatureArgs c = a;
         c.p = nullptr;
         hipError_t e = launch_expansion_packed(c, f64, stream);

@@ -213,9 +213,6 @@ struct YlmStream {
     }
 };
 
-__device__ __forceinline__ float fma_(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
-__device__ __forceinline__ double fma_(double x, double y, double z) { return __builtin_fma(x, y, z); }
-
 // Geometry of one pair: unit vector, 1/r, cutoff and its derivative, the
 // spline interval and local coordinate; a status on coincident atoms.
 template <typename T>
