@@ -1,4 +1,5 @@
-// Adjoint of the expansion with respect to positions with one lane per pair.
+// Adjoint of the expansion with respect to positions with one or two lanes
+// per pair.
 //
 // Adjoint (App. B Eq. energy-derivative), k_exp_backward_lanes: one wave per
 // centre i, one lane per pair q = (i, j, s).  With G = dL/dc_i (the

@@ -147,8 +147,8 @@ struct LaneLayout {
     int ch, np, nls, l2s, rs, ys, sp, cb, cs, total;
 };
 LaneLayout choose_lane_layout(int S, int nmax, int lmax, bool want_p, size_t elem);
-// c (and p when a.p is set) with one lane per pair; hipErrorNotSupported
-// when the layout does not fit
+// c (and p when a.p is set), a centre by one to four waves;
+// hipErrorNotSupported when the layout does not fit
 hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t stream);
 // c alone with the pairs of several centres packed into each wave's
 // chunks; hipErrorNotSupported when p is asked for or the layout does not fit
@@ -156,7 +156,7 @@ struct PackLayout {
     int G, gmax, total, cpw;
 };
 hipError_t launch_expansion_packed(const FeatureArgs& a, bool f64, hipStream_t stream);
-// per-pair dL/dr_ji of the adjoint with one lane per pair
+// per-pair dL/dr_ji of the adjoint with one or two lanes per pair
 bool expansion_backward_lanes_fits(const FeatureArgs& a, bool f64);
 hipError_t launch_expansion_backward_lanes(const FeatureArgs& a, bool f64, const void* grad_c, void* grad_pair,
                                            hipStream_t stream);
