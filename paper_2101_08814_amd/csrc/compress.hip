@@ -357,10 +357,60 @@ __device__ __forceinline__ void gram_tile(int nb, int64_t t, int64_t& bi, int64_
     bj = i + (t - (i * nb - i * (i - 1) / 2));
 }
 
-// part == NULL (one slice): C directly.  Otherwise slice s of tile t goes to
-// part[(s tiles + t) 4096 + ...] in the lanes' own order.
+// Four rows i0 .. i0 + 3 of column j of the kernel matrix to C, with their
+// mirror images where (off) the tile is not on the diagonal.  LOSS: the
+// differences to Kref instead; s1 and s2 gain (Kt - Kref)^2 and Kref^2.
+template <bool LOSS>
+__device__ __forceinline__ void gram_put(int n, int64_t i0, int64_t j, bool off, const tf::f32x4& a, float* C,
+                                         const float* Kref, double& s1, double& s2)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int64_t i = i0 + v;
+        if (i >= n || j >= n) continue;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {   // (i, j) and, off the diagonal tiles, (j, i)
+            if (m && !off) continue;
+            const int64_t e = m ? j * n + i : i * n + j;
+            if (LOSS) {
+                const double r = Kref[e], d = double(a[v]) - r;
+                C[e] = float(d);
+                s1 += d * d;
+                s2 += r * r;
+            } else {
+                C[e] = a[v];
+            }
+        }
+    }
+}
+
+// the work-group's sums of s1 and s2 to sums[2 block] and sums[2 block + 1]
+__device__ __forceinline__ void gram_sums(double s1, double s2, double* sums)
+{
+    __shared__ double red[2][4];
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        s1 += __shfl_xor(s1, o, 64);
+        s2 += __shfl_xor(s2, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][wave] = s1;
+        red[1][wave] = s2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        sums[2 * int64_t(blockIdx.x) + threadIdx.x] =
+            (red[threadIdx.x][0] + red[threadIdx.x][1]) + (red[threadIdx.x][2] + red[threadIdx.x][3]);
+}
+
+// part == NULL (one slice): C directly (LOSS: its difference to Kref, and the
+// sums).  Otherwise slice s of tile t goes to part[(s tiles + t) 4096 + ...]
+// in the lanes' own order.
+template <bool LOSS>
 __global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int64_t F, int64_t depth, int Q,
-                                                 const float* X, float* C, float* part)
+                                                 const float* X, float* C, float* part, const float* Kref,
+                                                 double* sums)
 {
     __shared__ tf::Smem sm;
     const int64_t tiles = int64_t(nb) * (nb + 1) / 2;
@@ -375,28 +425,22 @@ __global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int6
     w.init(Q, k0 + (threadIdx.x & 31));
     const int ra = n - i0 < tf::kTile ? int(n - i0) : tf::kTile, cb = n - j0 < tf::kTile ? int(n - j0) : tf::kTile;
     tf::product<true>(sm, X + i0 * F, F, ra, X + j0 * F, F, cb, k0, k1, w, acc);
-    if (part) {
+    if (!LOSS && part) {
         float* out = part + (int64_t(s) * tiles + t) * 4096 + (threadIdx.x >> 6) * 1024 + (threadIdx.x & 63) * 4;
 #pragma unroll
         for (int u = 0; u < 4; ++u) *reinterpret_cast<tf::f32x4*>(out + 256 * u) = acc[u >> 1][u & 1];
         return;
     }
+    double s1 = 0.0, s2 = 0.0;
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t i = i0 + tf::out_row(u >> 1) + v, j = j0 + tf::out_col(u & 1);
-            if (i < n && j < n) {
-                C[i * n + j] = acc[u >> 1][u & 1][v];
-                if (bi != bj) C[j * n + i] = acc[u >> 1][u & 1][v];
-            }
-        }
+        gram_put<LOSS>(n, i0 + tf::out_row(u >> 1), j0 + tf::out_col(u & 1), bi != bj, acc[u >> 1][u & 1], C, Kref, s1,
+                       s2);
+    if (LOSS) gram_sums(s1, s2, sums);
 }
 
 // Adds the slices in order: one lane per accumulator (four rows of one
-// column), four work-groups per tile.  With Kref the difference to it goes
-// to C instead, and sums[2 block], sums[2 block + 1] get this work-group's
-// sum of (Kt - Kref)^2 and of Kref^2.
+// column), four work-groups per tile.
 template <bool LOSS>
 __global__ void __launch_bounds__(256) k_gram_reduce(int n, int nb, int slices, const float* part, float* C,
                                                      const float* Kref, double* sums)
@@ -409,42 +453,10 @@ __global__ void __launch_bounds__(256) k_gram_reduce(int n, int nb, int slices, 
     for (int s = 1; s < slices; ++s) a += *reinterpret_cast<const tf::f32x4*>(src + s * tiles * 4096);
     int64_t bi, bj;
     gram_tile(nb, t, bi, bj);
-    const int64_t i0 = bi * tf::kTile + tf::out_row(u >> 1), j = bj * tf::kTile + tf::out_col(u & 1);
     double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int64_t i = i0 + v;
-        if (i >= n || j >= n) continue;
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {   // (i, j) and, off the diagonal tiles, (j, i)
-            if (m && bi == bj) continue;
-            const int64_t e = m ? j * n + i : i * n + j;
-            if (LOSS) {
-                const double r = Kref[e], d = double(a[v]) - r;
-                C[e] = float(d);
-                s1 += d * d;
-                s2 += r * r;
-            } else {
-                C[e] = a[v];
-            }
-        }
-    }
-    if (LOSS) {
-        __shared__ double red[2][4];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            s1 += __shfl_xor(s1, o, 64);
-            s2 += __shfl_xor(s2, o, 64);
-        }
-        if (lane == 0) {
-            red[0][wave] = s1;
-            red[1][wave] = s2;
-        }
-        __syncthreads();
-        if (threadIdx.x < 2)
-            sums[2 * int64_t(blockIdx.x) + threadIdx.x] =
-                (red[threadIdx.x][0] + red[threadIdx.x][1]) + (red[threadIdx.x][2] + red[threadIdx.x][3]);
-    }
+    gram_put<LOSS>(n, bi * tf::kTile + tf::out_row(u >> 1), bj * tf::kTile + tf::out_col(u & 1), bi != bj, a, C, Kref, s1,
+                   s2);
+    if (LOSS) gram_sums(s1, s2, sums);
 }
 
 __device__ __forceinline__ void loss_of(double d2, double r2, float* loss, float* scale)
@@ -1346,10 +1358,13 @@ GramSplit gram_split(int n, int Q, int lmax, bool split)
 
 }  // namespace
 
-// partial tiles of every slice, then the work-groups' loss sums
+// the partial tiles of every slice where there are several, then the
+// work-groups' loss sums.  One slice needs no tiles: they go to C, whose own
+// size they would reach (8.6 GB beside 17 GB at n = 65,536).
 size_t spectrum_gram_workspace(int n, int Q, int lmax)
 {
     const GramSplit g = gram_split(n, Q, lmax, true);
+    if (g.slices == 1) return size_t(g.tiles) * 2 * sizeof(double);
     return size_t(g.slices) * size_t(g.tiles) * 4096 * sizeof(float) + size_t(g.tiles) * 8 * sizeof(double);
 }
 
@@ -1357,8 +1372,8 @@ hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C
 {
     const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
     float* part = g.slices > 1 ? static_cast<float*>(ws) : nullptr;
-    hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F, g.depth,
-                       Q, X, C, part);
+    hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F,
+                       g.depth, Q, X, C, part, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
     if (part)
         hipLaunchKernelGGL(k_gram_reduce<false>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
                            part, C, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
@@ -1369,19 +1384,24 @@ hipError_t launch_spectrum_kernel_loss(int n, int Q, int lmax, const float* X, c
                                        float* loss, float* scale, float* dX, void* ws, hipStream_t stream)
 {
     const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
-    if (ws) {
-        // also with one slice: the tiles pass through the workspace so that
-        // the loss is summed by many work-groups
+    if (ws && g.slices == 1) {
+        double* sums = static_cast<double*>(ws);
+        hipLaunchKernelGGL(k_gram<true>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X,
+                           Kt, static_cast<float*>(nullptr), Kref, sums);
+        hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, g.tiles, sums, Kt, Kref, loss, scale);
+    } else if (ws) {
         float* part = static_cast<float*>(ws);
         double* sums = reinterpret_cast<double*>(part + size_t(g.slices) * g.tiles * 4096);
-        hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F,
-                           g.depth, Q, X, Kt, part);
+        hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices,
+                           g.F, g.depth, Q, X, Kt, part, static_cast<const float*>(nullptr),
+                           static_cast<double*>(nullptr));
         hipLaunchKernelGGL(k_gram_reduce<true>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
                            part, Kt, Kref, sums);
         hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, 4 * g.tiles, sums, Kt, Kref, loss, scale);
     } else {
-        hipLaunchKernelGGL(k_gram, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X, Kt,
-                           static_cast<float*>(nullptr));
+        hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X,
+                           Kt, static_cast<float*>(nullptr), static_cast<const float*>(nullptr),
+                           static_cast<double*>(nullptr));
         hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, int64_t(n) * n,
                            static_cast<const double*>(nullptr), Kt, Kref, loss, scale);
     }
