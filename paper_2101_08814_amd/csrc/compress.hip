@@ -406,9 +406,9 @@ __device__ __forceinline__ void gram_sums(double s1, double s2, double* sums)
 
 // part == NULL (one slice): C directly (LOSS: its difference to Kref, and the
 // sums).  Otherwise slice s of tile t goes to part[(s tiles + t) 4096 + ...]
-// in the lanes' own order.
+// in the lanes' own order.  A slice has `each` slabs of the inner dimension.
 template <bool LOSS>
-__global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int64_t F, int64_t depth, int Q,
+__global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int each, int more, int64_t F, int Q,
                                                  const float* X, float* C, float* part, const float* Kref,
                                                  double* sums)
 {
@@ -419,7 +419,9 @@ __global__ void __launch_bounds__(256, 2) k_gram(int n, int nb, int slices, int6
     int64_t bi, bj;
     gram_tile(nb, t, bi, bj);
     const int64_t i0 = bi * tf::kTile, j0 = bj * tf::kTile;
-    const int64_t k0 = s * depth, k1 = k0 + depth < F ? k0 + depth : F;
+    // the first `more` slices have one slab more than the others
+    const int64_t k0 = (int64_t(s) * each + (s < more ? s : more)) * tf::kSlab;
+    const int64_t ke = k0 + (each + (s < more ? 1 : 0)) * int64_t(tf::kSlab), k1 = ke < F ? ke : F;
     tf::f32x4 acc[2][2];
     tf::TriWeight w;
     w.init(Q, k0 + (threadIdx.x & 31));
@@ -1334,8 +1336,8 @@ namespace {
 // fill the chip, each slice at least kGramDeep slabs, in multiples of eight
 // (one set of columns per XCD) where that many fit
 struct GramSplit {
-    int nb, slices;
-    int64_t F, tiles, depth;
+    int nb, slices, each, more;
+    int64_t F, tiles;
 };
 
 GramSplit gram_split(int n, int Q, int lmax, bool split)
@@ -1350,9 +1352,10 @@ GramSplit gram_split(int n, int Q, int lmax, bool split)
     if (s > 64) s = 64;
     if (s >= 8) s = s / 8 * 8;
     if (s < 1) s = 1;
-    const int64_t slabs = (g.F + tf::kSlab - 1) / tf::kSlab;
-    g.depth = (slabs + s - 1) / s * tf::kSlab;
-    g.slices = int((g.F + g.depth - 1) / g.depth);   // non-empty slices
+    g.slices = int(s);
+    const int slabs = int((g.F + tf::kSlab - 1) / tf::kSlab);
+    g.each = slabs / g.slices;
+    g.more = slabs % g.slices;
     return g;
 }
 
@@ -1372,8 +1375,8 @@ hipError_t launch_spectrum_gram(int n, int Q, int lmax, const float* X, float* C
 {
     const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
     float* part = g.slices > 1 ? static_cast<float*>(ws) : nullptr;
-    hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.F,
-                       g.depth, Q, X, C, part, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
+    hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices, g.each,
+                       g.more, g.F, Q, X, C, part, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
     if (part)
         hipLaunchKernelGGL(k_gram_reduce<false>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
                            part, C, static_cast<const float*>(nullptr), static_cast<double*>(nullptr));
@@ -1386,20 +1389,20 @@ hipError_t launch_spectrum_kernel_loss(int n, int Q, int lmax, const float* X, c
     const GramSplit g = gram_split(n, Q, lmax, ws != nullptr);
     if (ws && g.slices == 1) {
         double* sums = static_cast<double*>(ws);
-        hipLaunchKernelGGL(k_gram<true>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X,
+        hipLaunchKernelGGL(k_gram<true>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.each, 0, g.F, Q, X,
                            Kt, static_cast<float*>(nullptr), Kref, sums);
         hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, g.tiles, sums, Kt, Kref, loss, scale);
     } else if (ws) {
         float* part = static_cast<float*>(ws);
         double* sums = reinterpret_cast<double*>(part + size_t(g.slices) * g.tiles * 4096);
         hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles * g.slices)), dim3(256), 0, stream, n, g.nb, g.slices,
-                           g.F, g.depth, Q, X, Kt, part, static_cast<const float*>(nullptr),
+                           g.each, g.more, g.F, Q, X, Kt, part, static_cast<const float*>(nullptr),
                            static_cast<double*>(nullptr));
         hipLaunchKernelGGL(k_gram_reduce<true>, dim3(unsigned(4 * g.tiles)), dim3(256), 0, stream, n, g.nb, g.slices,
                            part, Kt, Kref, sums);
         hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, 4 * g.tiles, sums, Kt, Kref, loss, scale);
     } else {
-        hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.F, g.depth, Q, X,
+        hipLaunchKernelGGL(k_gram<false>, dim3(unsigned(g.tiles)), dim3(256), 0, stream, n, g.nb, 1, g.each, 0, g.F, Q, X,
                            Kt, static_cast<float*>(nullptr), static_cast<const float*>(nullptr),
                            static_cast<double*>(nullptr));
         hipLaunchKernelGGL(k_kernel_loss, dim3(1), dim3(1024), 0, stream, int64_t(n) * n,

@@ -50,3 +50,14 @@ def test_many_tiles():
     G64 = 4 / n2 * (D @ X64) * w
     bound_G = 4 / n2 * w * ((bound_K + U * np.abs(D)) @ np.abs(X64) + (n + 8) * U * (np.abs(D) @ np.abs(X64)))
     assert np.all(np.abs(gX.double().cpu().numpy() - G64) <= bound_G)
+
+
+@pytest.mark.parametrize("n,Q,lmax", [(1, 8, 6), (256, 64, 6), (300, 48, 6), (64, 72, 6), (500, 32, 6), (700, 33, 12),
+                                      (900, 20, 2)])
+def test_slices_keep_to_the_xcds(n, Q, lmax):
+    """Eight slices or more are a multiple of eight, so that work-groups
+    that differ by eight (one XCD) take the same columns of X."""
+    tiles = -(-n // 64) * (-(-n // 64) + 1) // 2
+    bytes_ = workspace(n, Q, lmax)
+    slices = (bytes_ - 64 * tiles) / (16384 * tiles) if bytes_ > 64 * tiles else 1
+    assert slices == int(slices) and (slices < 8 or slices % 8 == 0)
