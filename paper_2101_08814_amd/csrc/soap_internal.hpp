@@ -153,7 +153,7 @@ hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t st
 // c alone with the pairs of several centres packed into each wave's
 // chunks; hipErrorNotSupported when p is asked for or the layout does not fit
 struct PackLayout {
-    int G, gmax, total, cpw;
+    int ch, gmax, total, cpw;   // pairs per chunk, quads of n per degree, LDS elements, centres per wave
 };
 hipError_t launch_expansion_packed(const FeatureArgs& a, bool f64, hipStream_t stream);
 // per-pair dL/dr_ji of the adjoint with one or two lanes per pair
