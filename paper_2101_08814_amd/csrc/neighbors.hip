@@ -868,13 +868,20 @@ __global__ void __launch_bounds__(64) k_fill1(NeighborArgs a)
 // box (one image when every width is at least 2 rcut) are tried, in
 // lexicographic order; the hit test is |r_j - r_i + s.H|^2 < rcut^2 in
 // double, as in the binned enumeration.  Counting and filling are two
-// launches; the fill ranks a centre's pairs by (species_j, j, s) in LDS,
-// as k_fill1 does, and forms the offsets from the counts itself.
+// launches; the fill orders a centre's pairs by (species_j, j, s) in LDS
+// (counting by species, or ranking as k_fill1 does) and forms the offsets from
+// the counts itself.
 constexpr int kBruteAtoms = 2048;
 constexpr int kBruteStructs = 64;
 constexpr int kBrutePerStruct = 256;
 constexpr int kBruteSortCap = 128;   // sort records per fill wave (more: sorted in global memory)
 constexpr int kBruteBatch = 4;   // rounds of 64 candidates whose positions are loaded together
+// A fill wave places its hits by counting them by species up to that many
+// species, by ranking the keys above: the count takes a step per species, the
+// ranking one per hit.  102,400 centres of 15 (60) pairs in cells of 200 atoms:
+// 4 species 231 (242) against 238 (298) us, 8 241 (251) and 238 (298), 16 263
+// (274) and 238 (298), 60 379 (396) and 238 (299).
+constexpr int kBruteCounted = 8;
 
 struct BruteCentre {
     bool ok;          // the whole input is valid
@@ -887,9 +894,9 @@ struct BruteCentre {
 };
 
 // Validity of the input and the centre's structure geometry (in gs).
-// GEOM: from the geometry phase (a.geom, a.ok; the structure found by a
-// binary search over the structures' ends, the same address in every
-// lane); otherwise built by the wave (at most 64 structures).
+// GEOM: from the geometry phase (a.geom, a.ok; the structure found by 64
+// probes of the structures' ends at a time); otherwise built by the wave (at
+// most 64 structures).
 template <bool GEOM>
 __device__ BruteCentre brute_centre(const NeighborArgs& a, int64_t i, StructGeom& gs)
 {
@@ -1170,10 +1177,10 @@ __global__ void __launch_bounds__(64) k_fill_bf(NeighborArgs a)
     };
     // in ascending j already, and every species valid (the count reports the
     // others): a stable count by species (the records of lane and lane + 64),
-    // one ballot per species
+    // one ballot per species, where these are few
     static_assert(kBruteSortCap == 128, "two records per lane");
     int sp[2] = {-1, -1};
-    bool counts = in_lds && single;
+    bool counts = in_lds && single && a.n_species <= kBruteCounted;
     if (counts) {
         bool bad = false;
 #pragma unroll
