@@ -24,10 +24,17 @@
 // each pair two lanes, 32 apart, each with half of the n: A, B and the five
 // sums are linear in G, so the halves add at the end, and only the harmonics
 // are formed twice.  1024 centres of 28 pairs at n=10, lmax=12 took 48 us,
-// 42 with the groups, 32 with the halves (at lmax 9 29, 24 and 20; in double
-// at lmax 8 36, 33 and 25).  At lower degrees, where two waves and more hide
-// each other's waits, the halves gain less (26.6, 22.1 and 19.1 at lmax 8 in
-// float) and one lane keeps the order of the sum over n.
+// 42 with the groups, 32 with the halves (in double at lmax 8 36, 33 and 25).
+// At lower degrees, where two waves and more hide each other's waits, the
+// halves gain less (26.6, 22.1 and 19.1 at lmax 8 in float) and one lane keeps
+// the order of the sum over n.  At lmax 9 in float the halves cost the second
+// wave that whole pairs keep, so they serve while every centre has a SIMD to
+// itself: 1024 centres of 28 pairs at n=9 take 21.1 us with them and 22.3
+// without, 4096 76 and 50.  With one n there is nothing to halve, and the
+// kernel without the code for it is the faster one (4096 centres at lmax 12:
+// 49.9 and 46.9 us).  In double the groups of two cost the second wave at lmax
+// 5 (4096 centres of 50 pairs at n=7: 48.7 us, 45.9 with single cubics); below
+// they gain (16,384 of 28 at n=4, lmax=2: 46.5, singly 51.5).
 #include "lane_pair.hpp"
 
 namespace soap {
@@ -39,14 +46,13 @@ using namespace dev;
 template <typename T>
 constexpr bool one_wave(int lmax) { return lmax > (sizeof(T) == 4 ? 8 : 5); }
 
-template <typename T, int LMAX>
-__global__ void __launch_bounds__(64, one_wave<T>(LMAX) ? 1 : 2)
+// GR: cubics per group; HALVES: two lanes per pair in chunks of at most 32;
+// WAVES: waves per SIMD that the registers keep
+template <typename T, int LMAX, int GR, bool HALVES, int WAVES>
+__global__ void __launch_bounds__(64, WAVES)
 k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c, T* __restrict__ grad_pair)
 {
     constexpr int LM1 = LMAX + 1, L2 = LM1 * LM1;
-    // cubics per group (of 1, 2, 3 and 4 the fastest in float; in double two
-    // cost the second wave where there is one)
-    constexpr int GR = sizeof(T) == 4 || one_wave<T>(LMAX) ? 2 : 1;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* G = reinterpret_cast<T*>(smem_raw);
     const int lane = threadIdx.x;
@@ -161,7 +167,7 @@ k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c, T* __restrict_
     };
     for (int64_t q0 = qb; q0 < qe; q0 += 64) {
         const int np = qe - q0 < 64 ? int(qe - q0) : 64;
-        if constexpr (one_wave<T>(LMAX)) {
+        if constexpr (HALVES) {
             if (np <= 32 && nmax > 1) {
                 chunk(std::true_type{}, q0, np);
                 continue;
@@ -173,20 +179,30 @@ k_exp_backward_lanes(FeatureArgs a, const T* __restrict__ grad_c, T* __restrict_
 
 template <typename T, int LM>
 struct BackLanesFn {
+    template <int GR, bool HALVES, int WAVES>
+    static hipError_t launch(const FeatureArgs& a, const void* grad_c, void* grad_pair, hipStream_t st)
+    {
+        const size_t lds = size_t(a.S) * a.nmax * (LM + 1) * (LM + 1) * sizeof(T);
+        auto kernel = k_exp_backward_lanes<T, LM, GR, HALVES, WAVES>;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_atoms)), dim3(64), lds, st, a, static_cast<const T*>(grad_c),
+                           static_cast<T*>(grad_pair));
+        return hipGetLastError();
+    }
     static hipError_t run(const FeatureArgs& a, const void* grad_c, void* grad_pair, hipStream_t st)
     {
+        constexpr bool f32 = sizeof(T) == 4;
         if constexpr (LM < 0) {
             return hipErrorNotSupported;
+        } else if constexpr (!one_wave<T>(LM)) {
+            return launch<f32 || LM < 5 ? 2 : 1, false, 2>(a, grad_c, grad_pair, st);
         } else {
-            const size_t lds = size_t(a.S) * a.nmax * (LM + 1) * (LM + 1) * sizeof(T);
-            if (lds > 65536) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_exp_backward_lanes<T, LM>),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-                if (e != hipSuccess) return e;
+            if constexpr (f32 && LM == 9) {
+                if (a.n_atoms > 1024 || a.nmax == 1) return launch<2, false, 2>(a, grad_c, grad_pair, st);
             }
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_exp_backward_lanes<T, LM>), dim3(unsigned(a.n_atoms)), dim3(64),
-                               lds, st, a, static_cast<const T*>(grad_c), static_cast<T*>(grad_pair));
-            return hipGetLastError();
+            if constexpr (f32 && LM > 9) {
+                if (a.nmax == 1) return launch<1, false, 1>(a, grad_c, grad_pair, st);
+            }
+            return launch<2, true, 1>(a, grad_c, grad_pair, st);
         }
     }
 };
