@@ -15,10 +15,8 @@
 // relative error of order 2^-16.
 //
 // W waves own one centre (W = 1, four centres per work-group, when C is
-// small and K <= 48; otherwise one centre per work-group, W = 4 up to K = 64
-// and W = 8 above, where the centre's LDS lets three work-groups share a CU:
-// 16,384 centres at K = 96, lmax 8: 851 -> 806 us): the
-// centre's waves split C into their LDS region as {H, L} pairs, then for
+// small and K <= 48; otherwise one centre per work-group of W = 4 or 8 waves,
+// see waves_per_centre): the centre's waves split C into their LDS region as {H, L} pairs, then for
 // each l run the 16 x 16 output tiles (I <= J) as three
 // v_mfma_f32_16x16x32_bf16 each (a lane reads 8 consecutive {H, L} words
 // of each of its two rows; one wave per centre reads every row block's
@@ -43,8 +41,7 @@ constexpr int kThreads = 256;
 constexpr int kLoadBatch = 16;   // coefficient loads a lane keeps in flight
 constexpr int kRows1 = 3;        // row blocks of 16 (K <= 48) a one-wave centre holds in registers
 constexpr int kStepsF32 = 7;     // 4-wide MFMA steps of a row of 2l+1 <= 25 values (lmax <= 12)
-constexpr int64_t kF32MfmaAtoms = 8192;   // FP32 spectra of at least this many centres, or of at least
-constexpr int kF32MfmaK = 24;              // this many channels, use the matrix cores
+constexpr int64_t kF32MfmaAtoms = 8192;   // FP32 spectra of at least this many centres use the matrix cores
 
 // round to nearest even (finite inputs)
 __device__ __forceinline__ unsigned short to_bf16(float f)
@@ -330,26 +327,50 @@ __global__ void __launch_bounds__(W > 4 ? 64 * W : kThreads) k_power_spectrum_f3
 }
 
 // LDS words of one centre's slot: {H, L} of C (or C), then the packed P_l
-size_t bf16_slot_words(int S, int nmax, int lmax, int W)
+size_t slot_words(int S, int nmax, int lmax)
 {
     const size_t K = size_t(S) * nmax, KL2 = K * (lmax + 1) * (lmax + 1), KK = K * (K + 1) / 2;
     return ((KL2 + 32 + 3) & ~size_t(3)) + ((KK + 3) & ~size_t(3));
 }
 
-// waves per centre: one when four centres' slots fit 40 KB of LDS (and
-// K <= 16 kRows1)
-int bf16_waves_per_centre(int S, int nmax, int lmax)
+// Waves per centre: one when four centres' slots fit 40 KB of LDS (and
+// K <= 16 kRows1), four otherwise up to K = 64.  Above, eight where four would
+// leave a CU under 20 waves (a slot over 32 KB: 16,384 centres at K = 96, lmax
+// 8 in bfloat16 851 us with four and 806 with eight; 4096 at K = 80, lmax 9
+// 186 and 174), or where the centres are few (100 at K = 66, lmax 4: 14.9 and
+// 11.4); four where their work-groups fill it (16,384 at K = 66, lmax 4: 244
+// and 288, in float 214 and 241).
+int waves_per_centre(int S, int nmax, int lmax, int64_t n_atoms)
 {
-    return 4 * 4 * bf16_slot_words(S, nmax, lmax, 1) <= 40 * 1024 && S * nmax <= 16 * kRows1 ? 1 : 4;
+    const int K = S * nmax;
+    const size_t slot = 4 * slot_words(S, nmax, lmax);
+    if (K <= 16 * kRows1 && 4 * slot <= 40 * 1024) return 1;
+    return K > 64 && (n_atoms <= 512 || slot > 32 * 1024) ? 8 : 4;
+}
+
+// FP32 spectra (without gradient rows) of fewer than kF32MfmaAtoms centres:
+// matrix cores or the VALU kernel.  At K = 96 (lmax 8) 100 centres take 22
+// against 74 us, 4096 217 against 374; K = 64 (lmax 6) 1000 centres 21 against
+// 31; K = 24 (lmax 6) 4096 centres 16 against 19; at K = 20 (lmax 8) 22.2
+// against 21.4, so fewer than 24 channels stay with the VALU.  So do
+// channels that leave much of their 16-wide blocks empty: with four waves per
+// centre and where the rows of c are odd, which the VALU kernel's LDS reads
+// like (lmax even; 4096 centres at K = 33, lmax 8 49 against 40 us, K = 27
+// lmax 8 35 against 29, K = 50 lmax 4 38 against 33; K = 36 lmax 9 60 against
+// 79; K = 24 also in between, lmax 9 37 against 34), but not few centres; with
+// one wave per centre and three blocks few centres (100 at K = 36, lmax 6
+// 12.9 against 10.8 us, 4096 26 against 33).
+bool f32_on_matrix_cores(int K, int lmax, int W, int64_t n_atoms)
+{
+    if (n_atoms >= kF32MfmaAtoms) return true;
+    if (K < 24) return false;
+    const bool third = K > 32 && K <= 38;   // a few channels in a third block
+    if (W == 1) return !(third && lmax >= 5 && n_atoms <= 1000);
+    if (n_atoms < 1000 || (lmax % 2 != 0 && K > 24)) return true;
+    return !(K <= 30 || third || ((K == 49 || K == 50) && lmax >= 2 && lmax <= 6));
 }
 
 }  // namespace
-
-size_t power_spectrum_bf16_lds(int S, int nmax, int lmax)
-{
-    const int W = bf16_waves_per_centre(S, nmax, lmax);
-    return size_t(kThreads / 64 / W) * 4 * bf16_slot_words(S, nmax, lmax, W);
-}
 
 template <int W, bool F32>
 hipError_t launch_mfma(const FeatureArgs& a, size_t lds, hipStream_t stream)
@@ -369,32 +390,27 @@ hipError_t launch_mfma(const FeatureArgs& a, size_t lds, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_power_spectrum_f32mfma(const FeatureArgs& a, hipStream_t stream)
+template <bool F32>
+hipError_t launch_mfma_waves(const FeatureArgs& a, hipStream_t stream)
 {
-    const size_t lds = power_spectrum_bf16_lds(a.S, a.nmax, a.lmax);
-    if (lds > 160 * 1024 || a.lmax > 12) return hipErrorNotSupported;
+    const int W = waves_per_centre(a.S, a.nmax, a.lmax, a.n_atoms);
+    const size_t lds = size_t(W == 1 ? 4 : 1) * 4 * slot_words(a.S, a.nmax, a.lmax);
+    if (lds > 160 * 1024 || (F32 && a.lmax > 12)) return hipErrorNotSupported;
     if (a.n_atoms == 0) return hipSuccess;
-    if (bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1) return launch_mfma<1, true>(a, lds, stream);
-    return a.S * a.nmax > 64 ? launch_mfma<8, true>(a, lds, stream) : launch_mfma<4, true>(a, lds, stream);
+    return W == 1   ? launch_mfma<1, F32>(a, lds, stream)
+           : W == 4 ? launch_mfma<4, F32>(a, lds, stream)
+                    : launch_mfma<8, F32>(a, lds, stream);
 }
 
 hipError_t launch_power_spectrum(const FeatureArgs& a, soap_precision prec, hipStream_t stream)
 {
-    // FP32 without gradient rows: FP32 operands on the matrix cores.  Against
-    // the VALU kernel, at K = 96 (lmax 8) 100 centres take 22 against 74 us,
-    // 4096 217 against 374; K = 64 (lmax 6) 1000 centres 23 against 34; K = 24
-    // 4096 centres 17 against 21; at K = 20 (lmax 8) 4096 centres 22.2 against
-    // 21.4, so fewer channels wait for kF32MfmaAtoms centres.
-    if (prec == SOAP_F32 && a.dp == nullptr && (a.n_atoms >= kF32MfmaAtoms || a.S * a.nmax >= kF32MfmaK)) {
-        const hipError_t e = launch_power_spectrum_f32mfma(a, stream);
+    if (prec == SOAP_F32 && a.dp == nullptr &&
+        f32_on_matrix_cores(a.S * a.nmax, a.lmax, waves_per_centre(a.S, a.nmax, a.lmax, a.n_atoms), a.n_atoms)) {
+        const hipError_t e = launch_mfma_waves<true>(a, stream);
         if (e != hipErrorNotSupported) return e;
     }
     if (prec != SOAP_BF16_F32ACC) return launch_power_spectrum_valu(a, prec == SOAP_F64, stream);
-    const size_t lds = power_spectrum_bf16_lds(a.S, a.nmax, a.lmax);
-    if (lds > 160 * 1024) return hipErrorNotSupported;
-    if (a.n_atoms == 0) return hipSuccess;
-    if (bf16_waves_per_centre(a.S, a.nmax, a.lmax) == 1) return launch_mfma<1, false>(a, lds, stream);
-    return a.S * a.nmax > 64 ? launch_mfma<8, false>(a, lds, stream) : launch_mfma<4, false>(a, lds, stream);
+    return launch_mfma_waves<false>(a, stream);
 }
 
 }  // namespace soap
