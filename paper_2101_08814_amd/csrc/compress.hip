@@ -1207,11 +1207,31 @@ size_t compress_bwd_lds(const CompressArgs& a)
                             4 * size_t(a.H) + QQ);
 }
 
+// Small networks on the work-group per centre rather than on the tiles of
+// compress_train.hip, which hold 128 hidden units and 16 to 32 columns whatever
+// the network needs: the work per column, H (K + Q) products, against tiles of
+// the same cost for all, fewer centres to a tile the higher the degree.
+// Forward, 2048 centres (16,384), lanes against tiles: K=8, H=20, Q=4, lmax 9
+// 45 (353) and 72 (501) us, K=16, H=16, Q=16 65 and 76, K=2, H=48, Q=4, lmax 4
+// 26 (191) and 25 (125), K=16, H=4, Q=16 18 and 26; 64 centres take 2 to 20
+// times as long by lanes.  Gradient, lmax 12: K=2, H=4, Q=4 225 and 307 us,
+// K=2, H=20, Q=4 284 and 308; at lmax 9 and below the tiles are faster.
+static bool small_network(const CompressArgs& a, bool backward)
+{
+    const int64_t work = int64_t(a.H) * (a.K + a.Q);
+    if (a.n < 1024 || a.K > 64) return false;
+    if (backward) return a.lmax >= 11 && work <= 100;
+    if (a.lmax >= 9) return work <= 520;
+    return a.n < 8192 ? work <= 400 : a.lmax >= 4 && work <= 150;
+}
+
 hipError_t launch_compress_forward(const CompressArgs& a, hipStream_t stream)
 {
     if (a.n == 0) return hipSuccess;
-    const hipError_t tiled = launch_train_forward(a, stream);
-    if (tiled != hipErrorNotSupported) return tiled;
+    if (!small_network(a, false)) {
+        const hipError_t tiled = launch_train_forward(a, stream);
+        if (tiled != hipErrorNotSupported) return tiled;
+    }
     const size_t lds = compress_fwd_lds(a);
     if (lds > 160 * 1024) return hipErrorNotSupported;
     auto kernel = a.ct ? (a.pt ? k_cmp_fwd<true, true> : k_cmp_fwd<true, false>) : k_cmp_fwd<false, true>;
@@ -1297,8 +1317,10 @@ hipError_t launch_compress_forward_bf16(const CompressArgs& a, hipStream_t strea
 
 hipError_t launch_compress_backward(const CompressArgs& a, float* grad, hipStream_t stream)
 {
-    const hipError_t tiled = launch_train_backward(a, grad, stream);
-    if (tiled != hipErrorNotSupported) return tiled;
+    if (!small_network(a, true)) {
+        const hipError_t tiled = launch_train_backward(a, grad, stream);
+        if (tiled != hipErrorNotSupported) return tiled;
+    }
     const size_t lds = compress_bwd_lds(a);
     if (lds > 160 * 1024) return hipErrorNotSupported;
     if (lds > 65536) {
