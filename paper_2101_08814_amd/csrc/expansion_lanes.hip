@@ -282,15 +282,23 @@ hipError_t launch_lanes(const FeatureArgs& a, const LaneLayout& W, hipStream_t s
 
 // Waves per centre for c and p: with one, fewer than 4096 centres leave most
 // of the chip's waves empty and each centre's sums and products run as one
-// chain.  Two are faster than one at every size measured (4000 centres of 45
-// pairs at n=10, lmax=8: 85 and 72 us, double 190 and 165; 1024 of 28 at
-// n=10, lmax=12: 30.2 and 25.8), four only while a CU has few centres: 21
-// centres of four species at n=8, lmax=6 take 19.0 us with one, 13.4 with two
-// and 11.2 with four, 512 float ones at n=9, lmax=6 15.8, 12.5 and 10.2, but
-// 512 in double at n=6, lmax=4 10.8, 10.0 and 10.3, and the 1024 above 33.2.
+// chain.  Two are faster than one (4000 centres of 45 pairs at n=10, lmax=8:
+// 85 and 72 us, double 190 and 165; 1024 of 28 at n=10, lmax=12: 30.2 and
+// 25.8), four only while a CU has few centres: 21 centres of four species at
+// n=8, lmax=6 take 19.0 us with one, 13.4 with two and 11.2 with four, 512
+// float ones at n=9, lmax=6 15.8, 12.5 and 10.2, but 512 in double at n=6,
+// lmax=4 10.8, 10.0 and 10.3, and the 1024 above 33.2.  One is enough where it
+// has an item for every lane and the centres are many: 3000 in double of 50
+// pairs and two species at n=6, lmax=4 (50 items) take 38.8 and 46.1 us with
+// one and two, 2000 33.7 and 33.0; in float two still hide each other's waits
+// there (3000: 23.3 and 19.1) but not with a quarter of a wave's items (3000 of
+// eight species at n=4, lmax=3: 28.0 and 31.3).
 // c alone comes here only for shapes that the packed kernel does not take,
 // at any number of centres: one wave.
 constexpr int64_t kFourWavesBytes = 2048;   // four waves up to that many centres times the element's size
+constexpr int64_t kOneWaveAtoms = 2500;     // one from that many centres, for at most kOneWaveItems items a species
+template <typename T>
+constexpr int kOneWaveItems = sizeof(T) == 8 ? 64 : 16;
 
 template <typename T, int LM>
 struct LanesFn {
@@ -300,6 +308,10 @@ struct LanesFn {
             return hipErrorNotSupported;
         } else {
             if (!want_p) return launch_lanes<T, LM, false, 1>(a, W, st);
+            if constexpr ((LM + 1) * (LM + 1) <= kOneWaveItems<T>) {
+                if (a.n_atoms >= kOneWaveAtoms && (W.np >> 2) * (LM + 1) * (LM + 1) <= kOneWaveItems<T>)
+                    return launch_lanes<T, LM, true, 1>(a, W, st);
+            }
             return a.n_atoms * int64_t(sizeof(T)) <= kFourWavesBytes ? launch_lanes<T, LM, true, 4>(a, W, st)
                                                                      : launch_lanes<T, LM, true, 2>(a, W, st);
         }
