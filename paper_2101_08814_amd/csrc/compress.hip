@@ -1034,6 +1034,9 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t i = int64_t(blockIdx.x) * W.cpw + wave;
     const bool live = i < a.n;
+    // units in the last pair of tiles: without, its columns are zeros also
+    // where c is not finite
+    const bool last = H > 32 * (KS2 - 1);
     const unsigned short* W1s = reinterpret_cast<const unsigned short*>(smem_raw + W.w1);
     const unsigned short* W2s = reinterpret_cast<const unsigned short*>(smem_raw + W.w2);
     const float* ab = reinterpret_cast<const float*>(smem_raw + W.ab);
@@ -1129,7 +1132,8 @@ __global__ void __launch_bounds__(kWaveCentres * 64) k_cmp_fwd_wave(CompressArgs
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     gt[(4 * g + v) * W.GS + 16 * u + r] =
-                        pack_bf16(h[ct][2 * u][v] * gate[2 * u], h[ct][2 * u + 1][v] * gate[2 * u + 1]);
+                        u < KS2 - 1 || last ? pack_bf16(h[ct][2 * u][v] * gate[2 * u], h[ct][2 * u + 1][v] * gate[2 * u + 1])
+                                            : 0u;
             wave_sync();
 #pragma unroll
             for (int pt = 0; pt < QT; ++pt) acc2[ct][pt] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -116,6 +116,9 @@ __global__ void __launch_bounds__(64, 2) k_cmp_infer(CompressArgs a, InferLayout
     const int K = a.K, Q = a.Q, H = a.H, lmax = a.lmax, L2 = (lmax + 1) * (lmax + 1);
     const int QQ = Q * (Q + 1) / 2;
     const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
+    // units in the last pair of tiles: without, its columns are zeros also
+    // where c is not finite
+    const bool last = H > 32 * (KS2 - 1);
     const int64_t i = blockIdx.x;
     unsigned* X = reinterpret_cast<unsigned*>(smem_raw);
     unsigned* gt = reinterpret_cast<unsigned*>(smem_raw + L.stage);
@@ -234,7 +237,7 @@ __global__ void __launch_bounds__(64, 2) k_cmp_infer(CompressArgs a, InferLayout
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         gt[(4 * g + v) * kHalf + 16 * u + r] =
-                            pack_bf16(h[ct][t][v] * gate[t], h[ct][t + 1][v] * gate[t + 1]);
+                            2 * hf + u < KS2 - 1 || last ? pack_bf16(h[ct][t][v] * gate[t], h[ct][t + 1][v] * gate[t + 1]) : 0u;
                 }
                 wave_sync();
 #pragma unroll
