@@ -274,11 +274,7 @@ template <int QT, int KS, int HT>
 hipError_t launch_infer_t(const CompressArgs& a, const InferLayout& L, hipStream_t stream)
 {
     auto kernel = k_cmp_infer<QT, KS, HT>;
-    if (L.total > 65536) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, L.total);
-        if (e != hipSuccess) return e;
-    }
+    // (at most 51 KB of LDS: K = 128, lmax 12)
     hipLaunchKernelGGL(kernel, dim3(unsigned(a.n)), dim3(64), size_t(L.total), stream, a, L);
     return hipGetLastError();
 }

@@ -1,16 +1,16 @@
-// Spherical expansion (and power spectrum) of a centre by one to four waves.
+// Spherical expansion and power spectrum of a centre by one to four waves.
 //
 // Expansion (Sec. 4.A Eq. spherical_expansion_coefficients_gaussians, Sec.
 // 4.F), k_expansion_lanes: one work-group of one, two or four waves per
 // centre.  For a chunk of up to 64 of its pairs, one to sixteen lanes per
 // pair form its harmonics Y_lm and radial values R_nl = f I~_nl in registers
-// and put them in the centre's LDS rows; then each lane owns items (four n, one lm) of a species block and sums
-// R_{n..n+3,l} Y_lm over the pairs of that species (one 16-byte and one
-// 4-byte LDS read per four FMAs).  Pairs arrive grouped by neighbour species
-// (the order soap_compute_neighbors writes), so a block is complete when the
-// species changes and is written then; a list that is not grouped is
-// detected and the centre is redone one species at a time.  With WANT_P the
-// blocks also go to an LDS copy of c_i and the power spectrum
+// and put them in the centre's LDS rows; then each lane owns items (four n,
+// one lm) of a species block and sums R_{n..n+3,l} Y_lm over the pairs of that
+// species (one 16-byte and one 4-byte LDS read per four FMAs).  Pairs arrive
+// grouped by neighbour species (the order soap_compute_neighbors writes), so a
+// block is complete when the species changes and is written then; a list that
+// is not grouped is detected and the centre is redone one species at a time.
+// The blocks stay in LDS as a copy of c_i, and the power spectrum
 // p_{l,k1<=k2} = sum_m c_{k1,lm} c_{k2,lm} (Sec. 2 Eq. nu2-basis-coupled up
 // to the factor of reading R4) is formed from it, one lane per (k1, k2).
 // Each output element has one owner: no atomics.
@@ -22,7 +22,7 @@ namespace {
 using namespace dev;
 
 // ------------------------------------------------------------- expansion
-template <typename T, int LMAX, bool WANT_P, int NW>
+template <typename T, int LMAX, int NW>
 __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, LaneLayout W)
 {
     constexpr int LM1 = LMAX + 1, L2 = LM1 * LM1;
@@ -64,16 +64,14 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
     // 4 ng..4 ng+3 of one lm, held in the block buffer blk4[v] (LDS) of the
     // species being summed; a lane takes items lane, lane + 64, ...
     V4<T>* const cs4 = reinterpret_cast<V4<T>*>(Cs);
-    auto block = [&](int sp) __attribute__((always_inline)) { return cs4 + (WANT_P ? sp * NI : 0); };
-    auto zero_block = [&](V4<T>* blk) __attribute__((always_inline)) {
-        for (int v = tid; v < NI; v += NT) blk[v] = V4<T>{T(0), T(0), T(0), T(0)};
+    auto zero_blocks = [&]() __attribute__((always_inline)) {
+        for (int v = tid; v < S * NI; v += NT) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
     };
     // species block sp of c to HBM with consecutive lanes on consecutive
     // addresses; the central atom adds its term to lm = 0 of its own species
-    // on the way (and, with WANT_P, to the LDS copy)
+    // on the way, and to the LDS copy
     auto flush = [&](int sp) __attribute__((always_inline)) {
-        V4<T>* blk = block(sp);
-        T* b1 = reinterpret_cast<T*>(blk);
+        T* b1 = reinterpret_cast<T*>(cs4 + sp * NI);
         sync();
         T* dst = c_out + sp * nL2;
         const bool own = sp == sp_i;
@@ -83,20 +81,16 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
             T v = *src;
             if (own && lm == 0) {
                 v += centre_term[n];
-                if (WANT_P) *src = v;
+                *src = v;
             }
             dst[e] = v;
         }
         sync();
-        if (!WANT_P) {
-            zero_block(blk);
-            sync();
-        }
     };
     // the chunk's pairs [lo, hi) of species sp added to its block: per item
     // and pair one 4-byte and one 16-byte LDS read and four FMAs
     auto accumulate = [&](int sp, int lo, int hi) __attribute__((always_inline)) {
-        V4<T>* blk = block(sp);
+        V4<T>* blk = cs4 + sp * NI;
         for (int v = tid; v < NI; v += NT) {
             const int ng = v / L2, lm = v - ng * L2;
             V4<T> s4 = blk[v];
@@ -116,11 +110,7 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
             blk[v] = s4;
         }
     };
-    if (WANT_P) {
-        for (int v = tid; v < S * NI; v += NT) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
-    } else {
-        zero_block(cs4);
-    }
+    zero_blocks();
 
     // Stages pairs q0 .. q0 + nc - 1 (harmonics and radial values in their
     // LDS rows); lane p < nc of every wave returns pair p's neighbour's
@@ -228,11 +218,7 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
         for (int sp = cur; sp < S; ++sp) flush(sp);
     } else {
         // pairs not grouped by species: every block, one species per pass
-        if (WANT_P) {
-            for (int v = tid; v < S * NI; v += NT) cs4[v] = V4<T>{T(0), T(0), T(0), T(0)};
-        } else {
-            zero_block(cs4);
-        }
+        zero_blocks();
         for (int sp = 0; sp < S; ++sp) {
             for (int64_t q0 = qb; q0 < qe; q0 += W.ch) {
                 const int nc = int(qe - q0 < W.ch ? qe - q0 : W.ch);
@@ -244,39 +230,31 @@ __global__ void __launch_bounds__(64 * NW) k_expansion_lanes(FeatureArgs a, Lane
             flush(sp);
         }
     }
-    if constexpr (WANT_P) {
-        sync();
-        const int K = S * nmax, KK = K * (K + 1) / 2;
-        T* p_out = static_cast<T*>(a.p) + i * int64_t(LM1 * KK);
-        for (int kk = tid; kk < KK; kk += NT) {
-            int k1, k2;
-            tri_decode(K, kk, k1, k2);
-            // c_{k, lm} sits at ((ng L2 + lm) 4 + n % 4) of species a's block
-            const int s1 = k1 / nmax, n1 = k1 - s1 * nmax, s2 = k2 / nmax, n2 = k2 - s2 * nmax;
-            const T* c1 = Cs + (s1 * NI + (n1 >> 2) * L2) * 4 + (n1 & 3);
-            const T* c2 = Cs + (s2 * NI + (n2 >> 2) * L2) * 4 + (n2 & 3);
-            static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
-                constexpr int L = decltype(Lc)::value;
-                T s = T(0);
+    sync();
+    const int K = S * nmax, KK = K * (K + 1) / 2;
+    T* p_out = static_cast<T*>(a.p) + i * int64_t(LM1 * KK);
+    for (int kk = tid; kk < KK; kk += NT) {
+        int k1, k2;
+        tri_decode(K, kk, k1, k2);
+        // c_{k, lm} sits at ((ng L2 + lm) 4 + n % 4) of species a's block
+        const int s1 = k1 / nmax, n1 = k1 - s1 * nmax, s2 = k2 / nmax, n2 = k2 - s2 * nmax;
+        const T* c1 = Cs + (s1 * NI + (n1 >> 2) * L2) * 4 + (n1 & 3);
+        const T* c2 = Cs + (s2 * NI + (n2 >> 2) * L2) * 4 + (n2 & 3);
+        static_for<0, LM1>([&](auto Lc) __attribute__((always_inline)) {
+            constexpr int L = decltype(Lc)::value;
+            T s = T(0);
 #pragma unroll
-                for (int m = L * L; m < (L + 1) * (L + 1); ++m) s += c1[4 * m] * c2[4 * m];
-                p_out[L * KK + kk] = s;
-            });
-        }
+            for (int m = L * L; m < (L + 1) * (L + 1); ++m) s += c1[4 * m] * c2[4 * m];
+            p_out[L * KK + kk] = s;
+        });
     }
 }
 
-template <typename T, int LM, bool WANT_P, int NW>
+template <typename T, int LM, int NW>
 hipError_t launch_lanes(const FeatureArgs& a, const LaneLayout& W, hipStream_t st)
 {
-    const size_t lds = size_t(W.total) * sizeof(T);
-    auto kernel = k_expansion_lanes<T, LM, WANT_P, NW>;
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_atoms)), dim3(64 * NW), lds, st, a, W);
+    auto kernel = k_expansion_lanes<T, LM, NW>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_atoms)), dim3(64 * NW), size_t(W.total) * sizeof(T), st, a, W);
     return hipGetLastError();
 }
 
@@ -293,8 +271,6 @@ hipError_t launch_lanes(const FeatureArgs& a, const LaneLayout& W, hipStream_t s
 // one and two, 2000 33.7 and 33.0; in float two still hide each other's waits
 // there (3000: 23.3 and 19.1) but not with a quarter of a wave's items (3000 of
 // eight species at n=4, lmax=3: 28.0 and 31.3).
-// c alone comes here only for shapes that the packed kernel does not take,
-// at any number of centres: one wave.
 constexpr int64_t kFourWavesBytes = 2048;   // four waves up to that many centres times the element's size
 constexpr int64_t kOneWaveAtoms = 2500;     // one from that many centres, for at most kOneWaveItems items a species
 template <typename T>
@@ -302,60 +278,50 @@ constexpr int kOneWaveItems = sizeof(T) == 8 ? 64 : 16;
 
 template <typename T, int LM>
 struct LanesFn {
-    static hipError_t run(const FeatureArgs& a, const LaneLayout& W, bool want_p, hipStream_t st)
+    static hipError_t run(const FeatureArgs& a, const LaneLayout& W, hipStream_t st)
     {
         if constexpr (LM < 0) {
             return hipErrorNotSupported;
         } else {
-            if (!want_p) return launch_lanes<T, LM, false, 1>(a, W, st);
             if constexpr ((LM + 1) * (LM + 1) <= kOneWaveItems<T>) {
                 if (a.n_atoms >= kOneWaveAtoms && (W.np >> 2) * (LM + 1) * (LM + 1) <= kOneWaveItems<T>)
-                    return launch_lanes<T, LM, true, 1>(a, W, st);
+                    return launch_lanes<T, LM, 1>(a, W, st);
             }
-            return a.n_atoms * int64_t(sizeof(T)) <= kFourWavesBytes ? launch_lanes<T, LM, true, 4>(a, W, st)
-                                                                     : launch_lanes<T, LM, true, 2>(a, W, st);
+            return a.n_atoms * int64_t(sizeof(T)) <= kFourWavesBytes ? launch_lanes<T, LM, 4>(a, W, st)
+                                                                     : launch_lanes<T, LM, 2>(a, W, st);
         }
     }
 };
 
 }  // namespace
 
-LaneLayout lane_layout(int S, int nmax, int lmax, bool want_p, int ch)
+LaneLayout lane_layout(int S, int nmax, int lmax, int ch)
 {
     LaneLayout W{};
     const int lm1 = lmax + 1, L2 = lm1 * lm1;
     W.ch = ch;
     W.np = (nmax + 3) & ~3;
-    // the last batch of eight radial values may run past nl: room for its
-    // offsets j + (np - nmax) floor(j / nmax)
-    int end = lm1 * W.np;
-    const int nl = lm1 * nmax;
-    for (int j = nl; j < ((nl + 7) & ~7); ++j) {
-        const int o = j + (W.np - nmax) * (j / nmax) + 1;
-        end = o > end ? o : end;
-    }
-    W.nls = (end + 3) & ~3;
+    W.nls = lm1 * W.np;
     W.l2s = L2 | 1;
     int o = 0;
     W.rs = o; o += ch * W.nls;
     W.ys = o; o += ch * W.l2s;
-    W.sp = o; o += ch;
     o = (o + 3) & ~3;
-    W.cb = W.np * L2;
-    W.cs = o; o += (want_p ? S : 1) * W.cb;
+    W.cs = o; o += S * W.np * L2;
     W.total = o;
     return W;
 }
 
-// Largest chunk (64, 32 or 16 pairs) whose per-wave LDS keeps at least six
-// waves per CU, else the smallest that fits 64 KB; total = 0 if none fits.
-LaneLayout choose_lane_layout(int S, int nmax, int lmax, bool want_p, size_t elem)
+// Largest chunk (64, 32 or 16 pairs) whose LDS keeps at least six centres'
+// work-groups per CU, else the smallest that fits 64 KB; total = 0 if none
+// fits.
+LaneLayout choose_lane_layout(int S, int nmax, int lmax, size_t elem)
 {
     for (int ch = 64; ch >= 16; ch /= 2) {
-        LaneLayout W = lane_layout(S, nmax, lmax, want_p, ch);
+        LaneLayout W = lane_layout(S, nmax, lmax, ch);
         if (size_t(W.total) * elem <= 24 * 1024) return W;
     }
-    LaneLayout W = lane_layout(S, nmax, lmax, want_p, 16);
+    LaneLayout W = lane_layout(S, nmax, lmax, 16);
     if (size_t(W.total) * elem > 64 * 1024) W.total = 0;
     return W;
 }
@@ -364,11 +330,8 @@ constexpr int64_t kSplitAtoms = 4096;   // c and p in two kernels from this many
 
 hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t stream)
 {
-    const bool want_p = a.p != nullptr;
-    if (!want_p) {
-        hipError_t e = launch_expansion_packed(a, f64, stream);
-        if (e != hipErrorNotSupported) return e;
-    } else if (a.n_atoms >= kSplitAtoms) {
+    if (a.p == nullptr) return launch_expansion_packed(a, f64, stream);
+    if (a.n_atoms >= kSplitAtoms) {
         // c with the pairs packed across centres, then p from c in HBM
         // (4096 liquid centres: 61 and 21 us against 78 for c and p in one
         // kernel, 8000 90 and 33 against 126; at n=6, lmax=4 in double 23 and
@@ -386,10 +349,10 @@ hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t st
         }
     }
     const size_t elem = f64 ? 8 : 4;
-    LaneLayout W = choose_lane_layout(a.S, a.nmax, a.lmax, want_p, elem);
+    LaneLayout W = choose_lane_layout(a.S, a.nmax, a.lmax, elem);
     if (W.total == 0 || a.n_atoms == 0) return W.total == 0 ? hipErrorNotSupported : hipSuccess;
-    return f64 ? by_degree<double, LanesFn>(a.lmax, a, W, want_p, stream)
-               : by_degree<float, LanesFn>(a.lmax, a, W, want_p, stream);
+    return f64 ? by_degree<double, LanesFn>(a.lmax, a, W, stream)
+               : by_degree<float, LanesFn>(a.lmax, a, W, stream);
 }
 
 }  // namespace soap

@@ -6,6 +6,8 @@ namespace soap {
 hipError_t launch_packed_f64(const FeatureArgs& a, const PackLayout& W, hipStream_t st);
 
 // Pairs per chunk and centres per wave; the results do not depend on them.
+// Chunks of 16 fit 64 KB of LDS at every nmax up to kPackMaxN, lmax and
+// precision (49 KB in double at nmax 16, lmax 12).
 //
 // Chunks of 32 pairs take half the steps of chunks of 16 and hold twice the
 // LDS.  While every centre has a wave of its own on the chip at once (256 CUs,
@@ -59,7 +61,6 @@ hipError_t launch_expansion_packed(const FeatureArgs& a, bool f64, hipStream_t s
     if (a.n_atoms == 0) return hipSuccess;
     const size_t elem = f64 ? 8 : 4;
     const PackLayout W = pack_layout(a.nmax, a.lmax, a.n_atoms, a.pair_capacity, elem);
-    if (size_t(W.total) * elem > 64 * 1024) return hipErrorNotSupported;
     return f64 ? launch_packed_f64(a, W, stream) : launch_packed<float>(a, W, stream);
 }
 

@@ -426,11 +426,6 @@ struct PackedFn {
     static hipError_t launch(const FeatureArgs& a, const PackLayout& W, hipStream_t st)
     {
         const size_t lds = size_t(W.total) * sizeof(T);
-        if (lds > 65536) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_expansion_packed<T, LM, GMAX, CH>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-            if (e != hipSuccess) return e;
-        }
         const int64_t waves = (a.n_atoms + W.cpw - 1) / W.cpw;
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_expansion_packed<T, LM, GMAX, CH>), dim3(unsigned(waves)), dim3(64), lds, st,
                            a, W);

@@ -139,14 +139,13 @@ struct RadialArgs {
 };
 hipError_t launch_radial(const RadialArgs& a, bool f64, hipStream_t stream);
 
-// Per-wave LDS layout of the one-lane-per-pair expansion (elements of T):
-// ch pairs of radial rows [lmax+1][np] and harmonic rows [l2s], and the
-// species blocks of c as [np/4][L2][4] (cb elements each): one buffer, or
-// with the power spectrum all S of them (an LDS copy of c_i).
+// LDS layout of the expansion with the power spectrum (elements of T), one per
+// centre: ch pairs of radial rows [lmax+1][np] and harmonic rows [l2s], and
+// the S species blocks of c as [np/4][L2][4].
 struct LaneLayout {
-    int ch, np, nls, l2s, rs, ys, sp, cb, cs, total;
+    int ch, np, nls, l2s, rs, ys, cs, total;
 };
-LaneLayout choose_lane_layout(int S, int nmax, int lmax, bool want_p, size_t elem);
+LaneLayout choose_lane_layout(int S, int nmax, int lmax, size_t elem);
 // c (and p when a.p is set), a centre by one to four waves;
 // hipErrorNotSupported when the layout does not fit
 hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t stream);
