@@ -32,7 +32,8 @@
 // products from global memory) took 329 us forward and 1518 us backward for
 // that batch; now 45 and 95 us, and 7.5 us for adding the partial sums
 // (17 us before, 64 serial loads per lane).  That form is kept (compress.hip)
-// for the shapes whose operands do not fit here: K or H over 128, Q over 32.
+// for the shapes whose operands do not fit here, K or H over 128, Q over 32,
+// and for small networks of many centres, which these tiles pad.
 #include "soap_internal.hpp"
 
 namespace soap {

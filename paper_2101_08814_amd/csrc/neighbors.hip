@@ -858,19 +858,22 @@ __global__ void __launch_bounds__(64) k_fill1(NeighborArgs a)
 }
 
 // ------------------------------------------------- small systems, all pairs
-// Systems of at most kBruteAtoms atoms in at most 64 structures of on
-// average at most kBrutePerStruct atoms: no bins.
-// A wave per centre checks the input itself (lane l builds the geometry of
-// structure l: the same checks as the bin build) and tests every atom j of
-// the centre's structure.  With f = (r_j - r_i) . Hinv the fractional
-// difference and w_k the width of the cell across lattice direction k, an
-// image s within rcut has |f_k + s_k| <= rcut / w_k, so only the s in that
-// box (one image when every width is at least 2 rcut) are tried, in
-// lexicographic order; the hit test is |r_j - r_i + s.H|^2 < rcut^2 in
-// double, as in the binned enumeration.  Counting and filling are two
-// launches; the fill orders a centre's pairs by (species_j, j, s) in LDS
-// (counting by species, or ranking as k_fill1 does) and forms the offsets from
-// the counts itself.
+// Structures of on average at most kBrutePerStruct atoms: no bins.  Of at most
+// kBruteAtoms atoms in at most kBruteStructs structures every wave checks the
+// input itself, of more the geometry phase does.  (The average was set on a
+// slower all-pairs form.  One cell of 1024 atoms of 28 pairs now takes 25.9 us
+// by all pairs and 29.6 by bins, of 2048 43.1 and 43.4, eight of 512 31 and 48,
+// eight of 1536 118 and 97.)
+// A wave per centre (checking: lane l builds the geometry of structure l, the
+// same checks as the bin build) tests every atom j of the centre's structure.
+// With f = (r_j - r_i) . Hinv the fractional difference and w_k the width of
+// the cell across lattice direction k, an image s within rcut has
+// |f_k + s_k| <= rcut / w_k, so only the s in that box (one image when every
+// width is at least 2 rcut) are tried, in lexicographic order; the hit test is
+// |r_j - r_i + s.H|^2 < rcut^2 in double, as in the binned enumeration.
+// Counting and filling are two launches; the fill orders a centre's pairs by
+// (species_j, j, s) in LDS (counting by species, or ranking as k_fill1 does)
+// and forms the offsets from the counts itself.
 constexpr int kBruteAtoms = 2048;
 constexpr int kBruteStructs = 64;
 constexpr int kBrutePerStruct = 256;

@@ -150,7 +150,8 @@ LaneLayout choose_lane_layout(int S, int nmax, int lmax, size_t elem);
 // hipErrorNotSupported when the layout does not fit
 hipError_t launch_expansion_lanes(const FeatureArgs& a, bool f64, hipStream_t stream);
 // c alone with the pairs of several centres packed into each wave's
-// chunks; hipErrorNotSupported when p is asked for or the layout does not fit
+// chunks, at every nmax, lmax and precision; hipErrorNotSupported when p is
+// asked for
 struct PackLayout {
     int ch, gmax, total, cpw;   // pairs per chunk, quads of n per degree, LDS elements, centres per wave
 };

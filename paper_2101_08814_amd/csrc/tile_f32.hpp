@@ -1,5 +1,7 @@
-// A 64 x 64 tile of C = A B in float on the matrix cores, for the products
-// of feature matrices (kernel matrices of spectra, the sparse model).
+// A 64 x 64 tile of C = A B in float on the matrix cores, for the kernel
+// matrices of spectra and the gradient of their loss.  (The sparse model has a
+// tile of its own, gpr.hip: on this one its two products of 1024 centres, 715
+// features and 2000 active points took 53 and 52 us against 51 and 48.)
 //
 // One work-group of four waves per tile; each wave owns a 32 x 32 quarter as
 // 2 x 2 accumulators of v_mfma_f32_16x16x4_f32 (lane (r, g) = (lane & 15,
