@@ -405,7 +405,7 @@ def measure_config(wl: str, steps: int, warmup: int):
         def ph_spectrum():
             state["p"] = calc.power_spectrum(state["c"], "bf16")
 
-        phases += [("expansion", ph_expansion, ("k_expansion_packed<float, 6, 2>", "expansion")),
+        phases += [("expansion", ph_expansion, ("k_expansion_packed<float, 6, 2, 16>", "expansion")),
                    ("spectrum_bf16_mfma", ph_spectrum, ("k_power_spectrum_bf16", "spectrum"))]
     else:
         out = calc.allocate_features(N, nl.capacity, td, dev, False)
@@ -415,9 +415,9 @@ def measure_config(wl: str, steps: int, warmup: int):
 
         tn = 'double' if td == torch.float64 else 'float'
         if N >= 4096:   # c with pairs packed across centres, then p from c (two kernels)
-            kname = f"k_expansion_packed<{tn}, {lmax}, {max(2, (nmax + 3) // 4)}> + k_power_spectrum<{tn}, false>"
+            kname = f"k_expansion_packed<{tn}, {lmax}, {(nmax + 3) // 4}, 16> + k_power_spectrum<{tn}, false>"
         else:
-            kname = f"k_expansion_lanes<{tn}, {lmax}, true>"
+            kname = f"k_expansion_lanes<{tn}, {lmax}, 2>"
         phases.append(("features", ph_features, (kname, "features")))
         if wl == "gpr":
             n_active, zeta = 2000, 4
